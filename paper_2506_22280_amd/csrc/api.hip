@@ -97,15 +97,26 @@ static int64_t default_capacity(int n, int T, int tile_px)
     return (int64_t)16 * (DIGS_TILE_PX / tile_px) * n * T + 4096;
 }
 
-// Workgroups per tile list when the caller leaves it open: a launch with few (view, tile) items
-// (one view, a small detector) leaves most SIMDs with one wave, so its lists are cut into slices
-// until there are about 4096 workgroups, at most DIGS_MAX_SLICES per list (one 256x256 view of
-// 50k Gaussians: forward 0.28 ms with one slice, 0.19 with 8, 0.17 with 16).
-static int default_slices(int64_t items)
+// Workgroups per tile list when the caller leaves it open. About 1024 splat workgroups (four per
+// CU) are resident at once. With fewer items than that, lists are cut until there are about 2048
+// (one 256x256 view of 50k Gaussians, 256 items: forward / backward splat 83 / 108 us whole, 55 / 68
+// with 4 slices, 41 / 59 with 8, 45 / 65 with 16; 540 items of 20k Gaussians: 93 / 115, 57 / 80 with
+// 4, 62 / 94 with 12), at most 8 unless the lists are long: a slice for every 600 entries that a list
+// is expected to hold, at a dozen tiles per Gaussian (80 items of 103k Gaussians: 56 / 69 us with 8,
+// 45 / 56 with 16; 480 items of 58k on a 86x55 detector: 205 / 197 with 4, 178 / 181 with 8). With
+// one to two resident rounds, long lists still gain by evening out the tiles (300k Gaussians,
+// 512x512, about 3500 entries a list: 156 / 263 -> 142 / 234 us with 3), short ones lose to the
+// partial images and their sum (80k: 76 / 140 -> 81 / 146): a slice for every thousand entries.
+static int default_slices(int64_t items, int n, int ntiles)
 {
     if (items >= 2048 || items <= 0) return 1;
-    const int64_t s = (4096 + items - 1) / items;
-    return (int)(s < DIGS_MAX_SLICES ? s : DIGS_MAX_SLICES);
+    const int64_t most = std::min<int64_t>(DIGS_MAX_SLICES, (4096 + items - 1) / items);
+    const int64_t entries = (int64_t)12 * n / ntiles;
+    const int64_t s = items >= 1024
+                          ? std::max<int64_t>(1, entries / 1000)
+                          : std::max(std::min<int64_t>(8, (2048 + items - 1) / items),
+                                     entries / 600);
+    return (int)std::min(s, most);
 }
 
 bool ws_layout(const digs_geom *geom, const digs_grid *grid, int n, int T,
@@ -122,7 +133,7 @@ bool ws_layout(const digs_geom *geom, const digs_grid *grid, int n, int T,
     L->T = T;
     L->R = grid->R;
     L->slices = (tuning && tuning->slices > 0) ? tuning->slices
-                                               : default_slices((int64_t)T * G.ntiles);
+                                               : default_slices((int64_t)T * G.ntiles, n, G.ntiles);
     // tile binning: smaller workgroups when the launch would have fewer than ~1024 of them
     {
         const int64_t full = (int64_t)(T > 0 ? T : 1) * ((n + DIGS_BIN_ITEMS - 1) / DIGS_BIN_ITEMS);

@@ -6,9 +6,10 @@
 //                    the projected record of the Gaussian's exact line integral (see below),
 //                    its cut-off bounding box and the detector tiles it touches
 //   k_bin_count/fill per projection, lists of Gaussians per 16x16 tile (bin.h)
-//   k_splat_fwd      one workgroup per (projection, tile), one wave per 8x8 pixel block; lane =
-//                    (Gaussian slot, column), eight Gaussians at a time, rows by forward
-//                    differences; every pixel is written once (no atomics)
+//   k_splat_fwd      one workgroup per (projection, tile), one wave per 8x8 pixel block, lane =
+//                    Gaussian, over the block's pixels by a polynomial of the exponent
+//                    (splat_poly.h), or, for Gaussians too narrow for it and short remainders,
+//                    lane = (Gaussian slot, column); every pixel is written once (no atomics)
 // Backward:
 //   k_splat_bwd      one lane per (list entry, 8x8 block) pair, looping over the block's 64 pixels
 //                    and accumulating 12 moment sums; one partial per instance (no atomics)
@@ -699,22 +700,208 @@ __device__ __forceinline__ void slice_range(uint32_t &begin, uint32_t &end, int 
 // a5: forward splat. One workgroup per (view, tile), one wave per 8x8 pixel block (with
 // WAVES == 1 a single wave takes the tile's four blocks in turn). The wave walks the tile's list
 // in chunks of 64 entries and appends the Gaussians whose footprint meets its block (bits of the
-// list entry) to one of three queues in LDS: those that meet both 4-row halves of the block, only
-// the upper, only the lower. It evaluates each queue 8 Gaussians at a time, over the rows its
-// Gaussians meet, and carries the remainder (fewer than 8) over to the next chunk, so that only
-// each queue's last group has idle lanes. lane = (Gaussian slot, column); each lane runs down the
-// rows of its column with forward differences of the two quadratic forms (two adds each per row).
-// The amplitude enters as log2|amp| added to the exponent (one multiply less per pixel); positive
-// and negative amplitudes go to separate row sums, the negative ones in a second pass that only
-// groups holding one take. The per-lane row sums are reduced over the 8 slots at the end in a
-// fixed order, and every pixel is written once.
-#define FWD_QUEUE (DIGS_WAVE + 8)
+// list entry) to one of two queues in LDS: those that meet both 4-row halves of the block, and
+// those that meet one. Whenever the first holds 64 Gaussians they are evaluated, one per lane, each
+// lane over its Gaussian's 64 pixels by the block polynomial (splat_poly.h) into 64 sums of its
+// own; those marked direct are set aside and evaluated by columns. The halves are evaluated at the
+// list's end, 32 pixels per Gaussian, their last partial group with the first queue's remainder. A
+// short remainder is evaluated by columns: lane = (Gaussian slot, column), eight Gaussians at a time, each lane down the rows of
+// its column by forward differences into 8 sums. The lanes' sums are added at the end in a fixed
+// order, and every pixel is written once.
+//
+// VALU-bound. A lane per Gaussian makes the set-up of its polynomial (80 instructions) a 64-pixel
+// one and each pixel 2.5 multiply-adds, an exp2 and one more multiply-add: 430 instructions for 64
+// Gaussians' blocks, against 8 x 84 by columns (a reciprocal square root, an exp2 and seven others
+// per pixel). By the same count a remainder of up to FWD_COLS Gaussians is cheaper by columns.
+// Measured against columns for all of them: 4.72 -> 3.70 ms (200k Gaussians, 64 views of 512x384),
+// 5.75 -> 4.33 (500k, 16 views of 1024x768), 127 -> 93 us (80k, 512x512), EWA 787 -> 739 us (200k,
+// 16 views of 512x384). Without the queue of halves the first takes 3.80 ms. A block most of whose
+// Gaussians are direct stays with the columns (splat_fwd_tile).
+#define FWD_QUEUE (2 * DIGS_WAVE)   // ring: fewer than 64 left over in each queue, and one chunk
+#define FWD_HALVES 512              // Gaussians that meet one half, kept to the list's end
+#define FWD_LDS (2 * FWD_QUEUE + FWD_HALVES)
+#define FWD_COLS 40
+
+// +1 or -1 with the sign of v
+__device__ __forceinline__ float sign_of(float v)
+{
+    return __uint_as_float((__float_as_uint(v) & 0x80000000u) | 0x3f800000u);
+}
+
+// Adds one pixel's value to the block's sums: NROWS == 8, row r of the block; NROWS == 4, row r of
+// either half, by the lane's weights of the two halves (0, or the amplitude's sign).
+template <int NROWS>
+__device__ __forceinline__ void add_pixel(float (&acc)[64], int r, int c, float v, float wu,
+                                          float wl)
+{
+    if (NROWS == 8) {
+        acc[8 * r + c] = fmaf(r < 4 ? wu : wl, v, acc[8 * r + c]);
+    } else {
+        acc[8 * r + c] = fmaf(wu, v, acc[8 * r + c]);
+        acc[8 * r + 32 + c] = fmaf(wl, v, acc[8 * r + 32 + c]);
+    }
+}
+
+// Evaluates the wave's records, one per lane (ent: the lane's queue entry, live: the lane has one),
+// over the block at (bx, by) (NROWS == 8) or over the half of it that each of them meets
+// (NROWS == 4) by the block polynomial. A queue entry is the byte offset of the Gaussian's record
+// and, in the low bits, the halves it meets (1 upper, 2 lower); with NROWS == 8 a half it does not
+// meet gets weight 0.
+template <bool EWA, int NROWS>
+__device__ __forceinline__ void splat_fwd_lanes(const float4 r0, const float4 r1, const float4 r2,
+                                                uint32_t ent, bool live, float bx, float by,
+                                                float (&acc)[64])
+{
+    const float sg = sign_of(r2.y);
+    const float wu = (ent & 1u) ? sg : 0.0f, wl = (ent & 2u) ? sg : 0.0f;
+    const float la = live ? r2.z : -INFINITY;   // (log2 0: adds zero)
+    const float cx = bx + 3.5f;
+    const float cy = (NROWS == 8 ? by : by + ((ent & 1u) ? 0.0f : 4.0f)) + 0.5f * (float)(NROWS - 1);
+    if constexpr (EWA) {
+        const float du = cx - r0.x, dv = cy - r0.y;
+        const float Huu = -fabsf(r0.z), mE = Huu * du, tE = fmaf(r0.w, dv, mE), nE = r1.x * dv;
+        const float E00 = fmaf(dv, nE, fmaf(du, tE, la)), E10 = tE + mE;
+        const float E01 = fmaf(r0.w, du, nE + nE);
+#pragma unroll
+        for (int rp = 0; rp < NROWS / 2; ++rp) {
+            const float t = (float)rp + 0.5f;
+            const float ev = fmaf(t * t, r1.x, E00);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const float k0 = fmaf(h == 0 ? t : -t, E01, ev);
+                const float k1 = fmaf(h == 0 ? t : -t, r0.w, E10);
+                const int r = h == 0 ? NROWS / 2 + rp : NROWS / 2 - 1 - rp;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float s = (float)c + 0.5f, e = fmaf(s * s, Huu, k0);
+                    add_pixel<NROWS>(acc, r, 4 + c, __builtin_amdgcn_exp2f(fmaf(s, k1, e)), wu, wl);
+                    add_pixel<NROWS>(acc, r, 3 - c, __builtin_amdgcn_exp2f(fmaf(-s, k1, e)), wu,
+                                     wl);
+                }
+                __builtin_amdgcn_sched_barrier(0);   // (a row at a time: registers)
+            }
+        }
+    } else {
+        BlockPoly b;
+        block_poly(r0, r1, r2, cx, cy, __ballot(mark_fold(r1)) != 0ull, b);
+        b.c[0] += la;
+        const float c40 = b.c[pidx(4, 0)];
+#pragma unroll
+        for (int rp = 0; rp < NROWS / 2; ++rp) {
+            float k[2][4];
+            poly_rows(b.c, (float)rp + 0.5f, k);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int r = h == 0 ? NROWS / 2 + rp : NROWS / 2 - 1 - rp;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    float xp, xm;
+                    poly_cols(k[h], c40, (float)c + 0.5f, xp, xm);
+                    add_pixel<NROWS>(acc, r, 4 + c, __builtin_amdgcn_exp2f(xp), wu, wl);
+                    add_pixel<NROWS>(acc, r, 3 - c, __builtin_amdgcn_exp2f(xm), wu, wl);
+                }
+                __builtin_amdgcn_sched_barrier(0);   // (a row at a time: registers)
+            }
+        }
+    }
+}
+
+// Evaluates cnt queued Gaussians from position head of the queue q (mask: its size less one for a
+// ring, else ~0) by columns, eight at a time, into the 8 row sums of the lane's column.
+template <bool EWA>
+__device__ __forceinline__ void splat_fwd_cols(const float4 *__restrict__ rt,
+                                               const uint32_t *__restrict__ q, int head, int cnt,
+                                               int mask, int lane, float bx, float by,
+                                               float (&accc)[8])
+{
+    const float fi = bx + (float)(lane & 7);
+    for (int j = 0; j < cnt; j += 8) {
+        // a slot past the queue's end repeats its last Gaussian with amplitude 0
+        const int sn = j + (lane >> 3);
+        const uint32_t ent = q[(head + min(sn, cnt - 1)) & mask];
+        const float4 *rg = (const float4 *)((const char *)rt + (ent & ~3u));
+        const float4 r0 = rg[0], r1 = rg[1], r2 = rg[2];
+        const float sg = sign_of(r2.y), la = sn < cnt ? r2.z : -INFINITY;
+        const float wu = (ent & 1u) ? sg : 0.0f, wl = (ent & 2u) ? sg : 0.0f;
+        const float du = fi - r0.x, dv0 = by - r0.y;
+        const float AE = -fabsf(r0.z) * du * du, BE = r0.w * du, CE = r1.x;
+        const float s1 = fmaf(2.0f, dv0, 1.0f);
+        float e = fmaf(dv0, fmaf(CE, dv0, BE), AE), de = fmaf(CE, s1, BE);
+        if constexpr (EWA) {
+            e += la;   // amp 2^E = 2^(E + log2 amp)
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                accc[r] = fmaf(r < 4 ? wu : wl, __builtin_amdgcn_exp2f(e), accc[r]);
+                e += de;
+                de += 2.0f * CE;
+            }
+        } else {
+            // amp rs 2^x = rs 2^(x + log2 amp); q is kept positive where a half that the
+            // footprint does not meet carries weight 0
+            const float Aq = fmaf(du, fmaf(fabsf(r1.w), du, r1.y), 1.0f);
+            const float Bq = fmaf(r2.x, du, r1.z), Cq = fabsf(r2.y);
+            float qv = fmaf(dv0, fmaf(Cq, dv0, Bq), Aq), dq = fmaf(Cq, s1, Bq);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const float rs = __builtin_amdgcn_rsqf(fmaxf(qv, 1.0e-20f));
+                const float v = rs * __builtin_amdgcn_exp2f(fmaf(e, rs * rs, la));
+                accc[r] = fmaf(r < 4 ? wu : wl, v, accc[r]);
+                qv += dq;
+                dq += 2.0f * Cq;
+                e += de;
+                de += 2.0f * CE;
+            }
+        }
+    }
+}
+
+__device__ __forceinline__ void wave_sync_lds()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int B, int PATTERN>
+__device__ __forceinline__ void transpose_step(float (&v)[64], int lane)
+{
+    const bool hi = (lane & B) != 0;
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+        const float keep = hi ? v[i + B] : v[i], send = hi ? v[i] : v[i + B];
+        v[i] = keep + __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(send), PATTERN));
+    }
+}
+
+// The lanes' 64 sums added over the wave in a fixed order: lane l returns the total of v[l]. Each
+// exchange halves the pixels a lane holds: over the wave's halves and the 16-lane rows by swapping
+// registers (v_permlane32_swap, v_permlane16_swap), within a row by swizzles.
+__device__ __forceinline__ float wave_transpose_sum(float (&v)[64], int lane)
+{
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]),
+                                                        __float_as_uint(v[i + 32]), false, false);
+        v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]),
+                                                        __float_as_uint(v[i + 16]), false, false);
+        v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    transpose_step<8, 0x201F>(v, lane);   // (swizzle patterns: xor the lane's low bits)
+    transpose_step<4, 0x101F>(v, lane);
+    transpose_step<2, 0x081F>(v, lane);
+    transpose_step<1, 0x041F>(v, lane);
+    return v[0];
+}
 
 // Adds rows [R0, R0 + NR) of one Gaussian at the lane's column into acc: from the row quadratics
 // q (and its first and second differences) and E, with la = log2|amp| (-inf: adds zero). EWA:
 // q = 1, so a pixel costs one exp2 and the E recurrence.
 template <bool EWA, int R0, int NR>
-__device__ __forceinline__ void splat_fwd_rows(float q, float dq, float ddq, float e, float de,
+__device__ __forceinline__ void splat_cols_rows(float q, float dq, float ddq, float e, float de,
                                                float dde, float la, float *acc)
 {
     if constexpr (EWA) {
@@ -745,18 +932,24 @@ __device__ __forceinline__ void splat_fwd_rows(float q, float dq, float ddq, flo
 // negative ones (by magnitude, in a second pass taken only when the group has any) into accn.
 // The queue holds the byte offsets of the Gaussians' records from rt.
 template <bool EWA, int R0, int NR, bool TAIL>
-__device__ __forceinline__ void splat_fwd_group(const float4 *__restrict__ rt,
+__device__ __forceinline__ void splat_cols_group(const float4 *__restrict__ rt,
                                                 const uint32_t *__restrict__ qid, int ns,
                                                 int gslot, float fi, float fby, float *acc,
                                                 float *accn)
 {
+    // (TAIL) a slot past the queue's end repeats its last Gaussian with amplitude 0
+    const float4 *rg = (const float4 *)((const char *)rt + qid[TAIL ? min(gslot, ns - 1) : gslot]);
+    float4 n0 = rg[0], n1 = rg[1], n2 = rg[2];   // (the next eight's records are on their way)
     for (int j = 0; j < ns; j += 8) {
-        // (TAIL) a slot past the queue's end repeats its last Gaussian with amplitude 0
         const int sn = j + gslot;
         const bool live = !TAIL || sn < ns;
-        const float4 *rg =
-            (const float4 *)((const char *)rt + qid[TAIL ? min(sn, ns - 1) : sn]);
-        const float4 r0 = rg[0], r1 = rg[1], r2 = rg[2];
+        const float4 r0 = n0, r1 = n1, r2 = n2;
+        if (!TAIL && j + 8 < ns) {
+            rg = (const float4 *)((const char *)rt + qid[sn + 8]);
+            n0 = rg[0];
+            n1 = rg[1];
+            n2 = rg[2];
+        }
         // r0 = (us, vs, Huu', Huv'), r1 = (Hvv', gu2, gv2, Guu),
         // r2 = (Guv2, Gvv, log2|amp|, -); the
         // signs of Huu', Guu and Gvv are marks
@@ -770,19 +963,224 @@ __device__ __forceinline__ void splat_fwd_group(const float4 *__restrict__ rt,
         const float e = fmaf(dv0, fmaf(CE, dv0, BE), AE);
         const float de = fmaf(CE, s1, BE);
         const bool neg = signbit(r2.y);
-        splat_fwd_rows<EWA, R0, NR>(q, dq, 2.0f * Cq, e, de, 2.0f * CE,
+        splat_cols_rows<EWA, R0, NR>(q, dq, 2.0f * Cq, e, de, 2.0f * CE,
                                     (live && !neg) ? r2.z : -INFINITY, acc);
         if (__ballot(live && neg) != 0ull)
-            splat_fwd_rows<EWA, R0, NR>(q, dq, 2.0f * Cq, e, de, 2.0f * CE,
+            splat_cols_rows<EWA, R0, NR>(q, dq, 2.0f * Cq, e, de, 2.0f * CE,
                                         (live && neg) ? r2.z : -INFINITY, accn);
     }
 }
 
-__device__ __forceinline__ void wave_sync_lds()
+// One wave's sums of its block at (bx, by) over list entries [begin, end), by columns throughout.
+// Three queues (LDS, FWD_COLS_QUEUE entries each): Gaussians that meet both halves of the block, only
+// the upper, only the lower; each is evaluated eight Gaussians at a time over the rows they meet, and
+// its remainder (fewer than 8) is carried over to the next chunk.
+#define FWD_COLS_QUEUE (DIGS_WAVE + 8)
+template <bool EWA>
+__device__ __forceinline__ float splat_cols_block(const float4 *__restrict__ rt,
+                                                  const uint32_t *__restrict__ list,
+                                                  uint32_t begin, uint32_t end, int n, int blkid,
+                                                  int lane, int bx, int by, uint32_t *lds)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    uint32_t(*qs)[FWD_COLS_QUEUE] = (uint32_t(*)[FWD_COLS_QUEUE])lds;
+    const int gslot = lane >> 3, col = lane & 7;
+    const float fi = (float)(bx + col), fby = (float)by;
+    float acc[8], accn[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) acc[r] = accn[r] = 0.0f;
+    // queued Gaussians carried over from earlier chunks (fewer than 8 per queue)
+    int pend0 = 0, pend1 = 0, pend2 = 0;
+    for (uint32_t c0 = begin; c0 < end; c0 += DIGS_WAVE) {
+        const uint32_t k = c0 + lane;
+        uint32_t g = 0, h = 0;
+        if (k < end) {
+            const uint32_t e = list[k];
+            g = e & LIST_INDEX_MASK;
+            h = g < (uint32_t)n ? (e >> (LIST_BLOCK_SHIFT + 2 * blkid)) & 3u : 0u;
+        }
+        const unsigned long long m0 = __ballot(h == 3u), m1 = __ballot(h == 1u),
+                                 m2 = __ballot(h == 2u);
+        // a masked store per queue (the empty asm keeps the compiler from merging them into
+        // one store whose queue, count and mask each lane selects)
+        // (the queues hold the records' byte offsets, g * 64 < 2^30)
+        const uint32_t go = g << 6;
+        if (h == 3u) qs[0][pend0 + lane_rank(m0)] = go;
+        asm volatile("" ::: "memory");
+        if (h == 1u) qs[1][pend1 + lane_rank(m1)] = go;
+        asm volatile("" ::: "memory");
+        if (h == 2u) qs[2][pend2 + lane_rank(m2)] = go;
+        const int ns0 = pend0 + __popcll(m0), ns1 = pend1 + __popcll(m1),
+                  ns2 = pend2 + __popcll(m2);
+        const int f0 = ns0 & ~7, f1 = ns1 & ~7, f2 = ns2 & ~7;
+        wave_sync_lds();
+        if (f0 > 0)
+            splat_cols_group<EWA, 0, 8, false>(rt, qs[0], f0, gslot, fi, fby, acc, accn);
+        if (f1 > 0)
+            splat_cols_group<EWA, 0, 4, false>(rt, qs[1], f1, gslot, fi, fby, acc, accn);
+        if (f2 > 0)
+            splat_cols_group<EWA, 4, 4, false>(rt, qs[2], f2, gslot, fi, fby, acc, accn);
+        if ((f0 | f1 | f2) > 0) {
+            // move each queue's remainder to its front: lane 8c + i moves entry i of queue c
+            const int qc = lane >> 3, qi = lane & 7;
+            const int fc = qc == 0 ? f0 : (qc == 1 ? f1 : f2);
+            const int lc = (qc == 0 ? ns0 : (qc == 1 ? ns1 : ns2)) - fc;
+            const bool mv = qc < 3 && qi < lc;
+            const uint32_t keep = mv ? qs[qc][fc + qi] : 0u;
+            wave_sync_lds();
+            if (mv) qs[qc][qi] = keep;
+            wave_sync_lds();
+        }
+        pend0 = ns0 - f0;
+        pend1 = ns1 - f1;
+        pend2 = ns2 - f2;
+    }
+    if (pend0 > 0)
+        splat_cols_group<EWA, 0, 8, true>(rt, qs[0], pend0, gslot, fi, fby, acc, accn);
+    if (pend1 > 0)
+        splat_cols_group<EWA, 0, 4, true>(rt, qs[1], pend1, gslot, fi, fby, acc, accn);
+    if (pend2 > 0)
+        splat_cols_group<EWA, 4, 4, true>(rt, qs[2], pend2, gslot, fi, fby, acc, accn);
+    wave_sync_lds();
+    // sum over the 8 Gaussian slots (lane bits 3..5) in a fixed order
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        acc[r] -= accn[r];
+        acc[r] += __shfl_xor(acc[r], 8, 64);
+        acc[r] += __shfl_xor(acc[r], 16, 64);
+        acc[r] += __shfl_xor(acc[r], 32, 64);
+    }
+    float v = acc[0];
+#pragma unroll
+    for (int r = 1; r < 8; ++r) v = (gslot == r) ? acc[r] : v;
+    return v;
+}
+
+// One wave's sums of its block at (bx, by) over list entries [begin, end): lane l returns pixel l.
+// next: the lane's entry of the first chunk (the last entry past the end).
+template <bool EWA>
+__device__ __forceinline__ float splat_fwd_block(const float4 *__restrict__ rt,
+                                                 const uint32_t *__restrict__ list, uint32_t begin,
+                                                 uint32_t end, int n, int blkid, int lane, int bx,
+                                                 int by, uint32_t next, uint32_t *lds)
+{
+    uint32_t *q0 = lds, *q1 = q0 + FWD_QUEUE, *q2 = q1 + FWD_HALVES;
+    float acc[64], accc[8];
+#pragma unroll
+    for (int p = 0; p < 64; ++p) acc[p] = 0.0f;
+#pragma unroll
+    for (int p = 0; p < 8; ++p) accc[p] = 0.0f;
+    const float fx = (float)bx, fy = (float)by;
+    bool lanes = false;        // whether any group went to the lanes' sums (uniform)
+    // queued Gaussians that meet both halves (a ring; fewer than 64 between chunks) and, kept
+    // for the second loop, those that meet one (any that q1 has no room for go to q0); in q2
+    // those set aside for the columns (fewer than 64)
+    int n0 = 0, h0 = 0, n1 = 0, n2 = 0;
+    uint32_t c0 = begin;
+    bool flush = false;
+    for (;;) {
+        // queue chunks until there is a group for the lanes; what is for the columns is
+        // evaluated on the way (so that the lanes' 64 sums change in one place per loop: with
+        // two, the compiler copies and spills them)
+        float4 r0, r1, r2;
+        uint32_t ent;
+        bool live = false;
+        int c = 0;
+        for (;;) {
+            if (n0 >= DIGS_WAVE || (flush && n0 > 0)) {
+                c = min(n0, DIGS_WAVE);
+                ent = q0[(h0 + min(lane, c - 1)) & (FWD_QUEUE - 1)];
+                const float4 *rg = (const float4 *)((const char *)rt + (ent & ~3u));
+                r0 = rg[0];
+                r1 = rg[1];
+                r2 = rg[2];
+                // Gaussians marked direct are set aside for the columns, or take the rest of
+                // their group with them if it would hold too few
+                const bool dir = !EWA && lane < c && mark_direct(r0);
+                const unsigned long long dm = EWA ? 0ull : __ballot(dir);
+                const bool cols = c - __popcll(dm) <= FWD_COLS;
+                live = lane < c && !dir;
+                if (!cols && dm != 0ull) {
+                    if (dir) q2[n2 + lane_rank(dm)] = ent;
+                    n2 += __popcll(dm);
+                    wave_sync_lds();
+                    if (n2 >= DIGS_WAVE) {
+                        splat_fwd_cols<EWA>(rt, q2, 0, n2, ~0, lane, fx, fy, accc);
+                        n2 = 0;
+                    }
+                }
+                if (cols)
+                    splat_fwd_cols<EWA>(rt, q0, h0, c, FWD_QUEUE - 1, lane, fx, fy, accc);
+                h0 = (h0 + c) & (FWD_QUEUE - 1);
+                n0 -= c;
+                if (!cols) break;
+                c = 0;
+            } else if (flush) {
+                break;
+            } else if (c0 >= end) {   // the halves' last, partial group joins the whole ones
+                const int rem = n1 & (DIGS_WAVE - 1);
+                n1 -= rem;
+                if (lane < rem) q0[(h0 + n0 + lane) & (FWD_QUEUE - 1)] = q1[n1 + lane];
+                n0 += rem;
+                flush = true;
+                wave_sync_lds();
+            } else {
+                const uint32_t e = next, g = e & LIST_INDEX_MASK;
+                const bool in = c0 + lane < end && g < (uint32_t)n;
+                // (the next chunk's entries are on their way while this one's groups are
+                // evaluated; loaded by every lane, so that only their use waits for them)
+                c0 += DIGS_WAVE;
+                next = list[min(c0 + lane, end - 1)];
+                const uint32_t h = in ? (e >> (LIST_BLOCK_SHIFT + 2 * blkid)) & 3u : 0u;
+                const bool room = n1 <= FWD_HALVES - DIGS_WAVE;
+                const bool whole = h == 3u || (h != 0u && !room), half = h != 0u && !whole;
+                const unsigned long long m0 = __ballot(whole), m1 = __ballot(half);
+                // (the record's byte offset, g * 64 < 2^30, and the halves; a masked store per
+                // queue: the empty asm keeps them from being merged into one)
+                const uint32_t go = (g << 6) | h;
+                if (whole) q0[(h0 + n0 + lane_rank(m0)) & (FWD_QUEUE - 1)] = go;
+                asm volatile("" ::: "memory");
+                if (half) q1[n1 + lane_rank(m1)] = go;
+                n0 += __popcll(m0);
+                n1 += __popcll(m1);
+                wave_sync_lds();
+            }
+        }
+        if (c == 0) break;
+        splat_fwd_lanes<EWA, 8>(r0, r1, r2, ent, live, fx, fy, acc);
+        lanes = true;
+    }
+    // the full groups of halves
+    for (int k = 0;;) {
+        float4 r0, r1, r2;
+        uint32_t ent;
+        for (; k < n1; k += DIGS_WAVE) {
+            ent = q1[k + lane];
+            const float4 *rg = (const float4 *)((const char *)rt + (ent & ~3u));
+            r0 = rg[0];
+            r1 = rg[1];
+            r2 = rg[2];
+            if (EWA || __ballot(mark_direct(r0)) == 0ull) break;
+            splat_fwd_cols<EWA>(rt, q1, k, DIGS_WAVE, ~0, lane, fx, fy, accc);
+        }
+        if (k >= n1) break;
+        k += DIGS_WAVE;
+        splat_fwd_lanes<EWA, 4>(r0, r1, r2, ent, true, fx, fy, acc);
+        lanes = true;
+    }
+    if (n2 > 0) splat_fwd_cols<EWA>(rt, q2, 0, n2, ~0, lane, fx, fy, accc);
+    wave_sync_lds();
+    // the columns' sums over the 8 Gaussian slots (lane bits 3..5), then the lanes' sums
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        accc[r] += __shfl_xor(accc[r], 8, 64);
+        accc[r] += __shfl_xor(accc[r], 16, 64);
+        accc[r] += __shfl_xor(accc[r], 32, 64);
+    }
+    float v = accc[0];
+#pragma unroll
+    for (int r = 1; r < 8; ++r) v = ((lane >> 3) == r) ? accc[r] : v;
+    if (lanes) v += wave_transpose_sum(acc, lane);
+    return v;
 }
 
 // With nsl > 1 the workgroup renders slice sl of the tile's list into its own partial image
@@ -793,20 +1191,17 @@ __device__ __forceinline__ void splat_fwd_tile(const DevGeom &G, int n, int t, i
                                                const uint32_t *__restrict__ list,
                                                const uint32_t *__restrict__ cnt, int nblk,
                                                unsigned cap, float *__restrict__ proj,
-                                               uint32_t (*ids)[3][FWD_QUEUE], int sl, int nsl,
+                                               uint32_t (*ids)[FWD_LDS], int sl, int nsl,
                                                int T, float *__restrict__ spart)
 {
     const int tx = tile % G.tiles_x, ty = tile / G.tiles_x;
     const int wave = uniform((int)(threadIdx.x / DIGS_WAVE)), lane = lane_id();
-    const int gslot = lane >> 3, col = lane & 7;
     const size_t cidx = ((size_t)t * G.ntiles + tile) * nblk;
     uint32_t begin = cnt[cidx], end = cnt[cidx + nblk];
     begin = min(begin, cap);
     end = min(max(end, begin), cap);
     slice_range(begin, end, sl, nsl, DIGS_WAVE);
     const float4 *rt = rec + (size_t)t * n * 4;
-    // the wave's three queues: Gaussians that meet rows 0-7 of the block, only rows 0-3, only 4-7
-    uint32_t(*qs)[FWD_QUEUE] = ids[wave];
     // WAVES > 1 is launched only with one wave per block of the tile; a single wave takes the
     // tile's blocks in turn
     const int lbx = G.tile_lw - 3;   // log2 of the blocks per tile row
@@ -815,75 +1210,22 @@ __device__ __forceinline__ void splat_fwd_tile(const DevGeom &G, int n, int t, i
         const int blkid = WAVES > 1 ? wave : pass;
         const int bx = tx * G.tile_w + (blkid & (G.tile_bx - 1)) * 8;
         const int by = ty * G.tile_h + (blkid >> lbx) * 8;
-        const float fi = (float)(bx + col), fby = (float)by;
-        float acc[8], accn[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) acc[r] = accn[r] = 0.0f;
-        // queued Gaussians carried over from earlier chunks (fewer than 8 per queue)
-        int pend0 = 0, pend1 = 0, pend2 = 0;
-        for (uint32_t c0 = begin; c0 < end; c0 += DIGS_WAVE) {
-            const uint32_t k = c0 + lane;
-            uint32_t g = 0, h = 0;
-            if (k < end) {
-                const uint32_t e = list[k];
-                g = e & LIST_INDEX_MASK;
-                h = g < (uint32_t)n ? (e >> (LIST_BLOCK_SHIFT + 2 * blkid)) & 3u : 0u;
-            }
-            const unsigned long long m0 = __ballot(h == 3u), m1 = __ballot(h == 1u),
-                                     m2 = __ballot(h == 2u);
-            // a masked store per queue (the empty asm keeps the compiler from merging them into
-            // one store whose queue, count and mask each lane selects)
-            // (the queues hold the records' byte offsets, g * 64 < 2^30)
-            const uint32_t go = g << 6;
-            if (h == 3u) qs[0][pend0 + lane_rank(m0)] = go;
-            asm volatile("" ::: "memory");
-            if (h == 1u) qs[1][pend1 + lane_rank(m1)] = go;
-            asm volatile("" ::: "memory");
-            if (h == 2u) qs[2][pend2 + lane_rank(m2)] = go;
-            const int ns0 = pend0 + __popcll(m0), ns1 = pend1 + __popcll(m1),
-                      ns2 = pend2 + __popcll(m2);
-            const int f0 = ns0 & ~7, f1 = ns1 & ~7, f2 = ns2 & ~7;
-            wave_sync_lds();
-            if (f0 > 0)
-                splat_fwd_group<EWA, 0, 8, false>(rt, qs[0], f0, gslot, fi, fby, acc, accn);
-            if (f1 > 0)
-                splat_fwd_group<EWA, 0, 4, false>(rt, qs[1], f1, gslot, fi, fby, acc, accn);
-            if (f2 > 0)
-                splat_fwd_group<EWA, 4, 4, false>(rt, qs[2], f2, gslot, fi, fby, acc, accn);
-            if ((f0 | f1 | f2) > 0) {
-                // move each queue's remainder to its front: lane 8c + i moves entry i of queue c
-                const int qc = lane >> 3, qi = lane & 7;
-                const int fc = qc == 0 ? f0 : (qc == 1 ? f1 : f2);
-                const int lc = (qc == 0 ? ns0 : (qc == 1 ? ns1 : ns2)) - fc;
-                const bool mv = qc < 3 && qi < lc;
-                const uint32_t keep = mv ? qs[qc][fc + qi] : 0u;
-                wave_sync_lds();
-                if (mv) qs[qc][qi] = keep;
-                wave_sync_lds();
-            }
-            pend0 = ns0 - f0;
-            pend1 = ns1 - f1;
-            pend2 = ns2 - f2;
+        // A block of whose first 64 entries more than 8 are marked direct goes by columns
+        // throughout: setting them aside costs more than the lanes gain (58k Gaussians, 20 views
+        // of 86x55 pixels of 4.5 mm, nearly all direct: 131 us by columns, 155 by this rule, 185
+        // without it; 200k on 1 mm pixels, nearly none: 4.72 ms by columns, 3.70 by this rule)
+        uint32_t first = LIST_INDEX_MASK;
+        if (begin < end) first = list[min(begin + lane, end - 1)];
+        bool cols = false;
+        if constexpr (!EWA) {
+            const uint32_t g = first & LIST_INDEX_MASK;
+            const float huu = g < (uint32_t)n ? rt[(size_t)g * 4].z : -1.0f;
+            cols = 8 * __popcll(__ballot(!signbit(huu))) > DIGS_WAVE;
         }
-        if (pend0 > 0)
-            splat_fwd_group<EWA, 0, 8, true>(rt, qs[0], pend0, gslot, fi, fby, acc, accn);
-        if (pend1 > 0)
-            splat_fwd_group<EWA, 0, 4, true>(rt, qs[1], pend1, gslot, fi, fby, acc, accn);
-        if (pend2 > 0)
-            splat_fwd_group<EWA, 4, 4, true>(rt, qs[2], pend2, gslot, fi, fby, acc, accn);
-        wave_sync_lds();
-        // sum over the 8 Gaussian slots (lane bits 3..5) in a fixed order
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            acc[r] -= accn[r];
-            acc[r] += __shfl_xor(acc[r], 8, 64);
-            acc[r] += __shfl_xor(acc[r], 16, 64);
-            acc[r] += __shfl_xor(acc[r], 32, 64);
-        }
-        float v = acc[0];
-#pragma unroll
-        for (int r = 1; r < 8; ++r) v = (gslot == r) ? acc[r] : v;
-        const int px = bx + col, py = by + gslot;
+        float v;
+        if (cols) v = splat_cols_block<EWA>(rt, list, begin, end, n, blkid, lane, bx, by, ids[wave]);
+        else v = splat_fwd_block<EWA>(rt, list, begin, end, n, blkid, lane, bx, by, first, ids[wave]);
+        const int px = bx + (lane & 7), py = by + (lane >> 3);
         if (nsl > 1) {
             const int p = (py - ty * G.tile_h) * G.tile_w + (px - tx * G.tile_w);
             spart[(((size_t)sl * T + t) * G.ntiles + tile) * (G.tile_w * G.tile_h) + p] = v;
@@ -918,7 +1260,7 @@ __device__ __forceinline__ int next_item(uint32_t *__restrict__ queue, int home,
 
 // blockIdx.x: (view, tile); blockIdx.y: slice of the tile's list (gridDim.y slices)
 template <int WAVES, bool EWA>
-__global__ __launch_bounds__(64 * WAVES) void k_splat_fwd(DevGeom G, int n, int T,
+__global__ __launch_bounds__(64 * WAVES, 4) void k_splat_fwd(DevGeom G, int n, int T,
                                                           const float4 *__restrict__ rec,
                                                           const uint32_t *__restrict__ list,
                                                           const uint32_t *__restrict__ cnt,
@@ -926,7 +1268,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_splat_fwd(DevGeom G, int n, int 
                                                           float *__restrict__ proj,
                                                           float *__restrict__ spart)
 {
-    __shared__ uint32_t ids[WAVES][3][FWD_QUEUE];
+    __shared__ uint32_t ids[WAVES][FWD_LDS];
     int t, tile;
     map_block(blockIdx.x, G.ntiles, T, t, tile);
     splat_fwd_tile<WAVES, EWA>(G, n, t, tile, rec, list, cnt, nblk, cap, proj, ids, blockIdx.y,
@@ -963,18 +1305,18 @@ __global__ __launch_bounds__(256) void k_slice_reduce(DevGeom G, int T, int nsl,
 
 // Persistent variant: a grid sized to the machine loops over the work queues.
 template <int WAVES, bool EWA>
-__global__ __launch_bounds__(64 * WAVES) void k_splat_fwd_persist(
+__global__ __launch_bounds__(64 * WAVES, 4) void k_splat_fwd_persist(
     DevGeom G, int n, int T, const float4 *__restrict__ rec, const uint32_t *__restrict__ list,
     const uint32_t *__restrict__ cnt, int nblk, unsigned cap, float *__restrict__ proj,
     uint32_t *__restrict__ queue)
 {
-    __shared__ uint32_t ids[WAVES][3][FWD_QUEUE];
+    __shared__ uint32_t ids[WAVES][FWD_LDS];
     __shared__ int s_item;
     const int home = blockIdx.x & 7;
     for (;;) {
         if (threadIdx.x == 0) s_item = next_item(queue, home, G.ntiles, T);
         __syncthreads();
-        const int item = s_item;
+        const int item = uniform(s_item);
         __syncthreads();
         if (item < 0) break;
         int t, tile;
@@ -1516,7 +1858,7 @@ __global__ __launch_bounds__(256, 4) void k_splat_bwd_persist(
     for (;;) {
         if (threadIdx.x == 0) s_item = next_item(queue, home, G.ntiles, T);
         __syncthreads();
-        const int item = s_item;
+        const int item = uniform(s_item);
         __syncthreads();
         if (item < 0) break;
         int t, tile;

@@ -15,14 +15,16 @@
 // 6 mm). Folding the degree-5 terms into the lower ones (each power replaced by its closest lower
 // polynomial over the block's pixel positions, the log to third order) leaves an eighth. The set-up
 // evaluates the bound per (view, Gaussian) and marks the record: up to POLY_PLAIN the plain series
-// is as close as the FP32 evaluation by forward differences, up to POLY_FOLD the folded one is, and
-// a group that holds a record above that is evaluated directly.
+// is as close as the FP32 evaluation by forward differences, up to POLY_FOLD the folded one and the
+// moments taken with it are, and records above that are evaluated directly. (With 1.2e-5 and 4e-5
+// for POLY_FOLD single rotation gradients of sub-pixel Gaussians, out of 288k, moved by 1.5e-3 of
+// their root mean square; with 4e-6 by 4e-4, with no polynomial and another order of sums by 3e-4.)
 #pragma once
 
 #include "common.h"
 
 #define POLY_PLAIN 2.0e-6f
-#define POLY_FOLD 4.0e-5f
+#define POLY_FOLD 4.0e-6f
 #define POLY_HL 0.72134752044448170f   // log2(e) / 2
 
 // Index of s^i t^j (i + j <= 4) among the 15 coefficients and moments.
