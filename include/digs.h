@@ -337,7 +337,7 @@ int digs_phi_grid(const digs_grid *grid, const float *coef, int n, const float *
  *   meas [T][npix], h [R] (device) -> out [T][R(R+1)/2 + R + 1]: J^T J (upper triangle, row-major),
  *   J^T res, res.res with J_r = (I_r - I_0)/h_r, res = I_0 - P. Fixed-order sums.
  * digs_gemm_bf16: C[M][N] = A . B with A [M][K] (lda; transA: stored [K][M]) and B [K][N] (ldb;
- *   transB: stored [N][K]), FP32 in memory, BF16 operands on MFMA (v_mfma_f32_32x32x16_bf16), FP32
+ *   transB: stored [N][K]), FP32 in memory, BF16 operands on MFMA (v_mfma_f32_16x16x32_bf16), FP32
  *   accumulate; then, in order, + C if accumulate, + bias[N] if bias, max(., 0) if relu, 0 where
  *   gate[M][N] (leading dimension ldc) is <= 0 if gate.
  * digs_colsum: out[N] = column sums of X [M][N] (ldx). digs_mse: mean of

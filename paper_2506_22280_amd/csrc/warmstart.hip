@@ -9,95 +9,209 @@
 #include "kernels.h"
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-// float -> bfloat16, round to nearest even (finite inputs)
-__device__ __forceinline__ __bf16 to_bf16(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return __builtin_bit_cast(__bf16, (unsigned short)(u >> 16));
-}
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------------------------------
 // C[M][N] = epilogue(A . B) with op(A) [M][K] and op(B) [K][N] read from FP32 memory, rounded to
-// BF16 in LDS and multiplied on v_mfma_f32_32x32x16_bf16 with FP32 accumulation. A is stored
+// BF16 in registers and multiplied on v_mfma_f32_16x16x32_bf16 with FP32 accumulation. A is stored
 // [M][K] (lda) or, with TA, [K][M]; B is stored [K][N] (ldb) or, with TB, [N][K]. Epilogue, in
 // order: + C (accumulate), + bias[col], max(., 0) (relu), zero where gate[row][col] <= 0 (gate has
-// the leading dimension ldc). One workgroup (4 waves) per 64x64 tile of C, each wave a 32x32 block;
-// K is staged through LDS 32 at a time.
-#define GT_M 64
-#define GT_N 64
+// the leading dimension ldc).
+//
+// A wave computes 16 rows by 16 TN columns, from operands that its lanes load straight into the
+// matrix cores' layout: the products of the warm-start network are latency-bound, with few tiles
+// of C or few steps of K, so there is little reuse for a staged tile to serve and no barrier in
+// the loop. Column TN * (l % 16) + j of the wave's tile is column l % 16 of its j-th matrix, which
+// makes a lane's TN columns adjacent in memory. KW waves of a workgroup share a tile, wave w
+// taking the 32-wide steps w, w + KW, ... of K, and their sums are added in wave order; with
+// KW == 1 the workgroup's four waves take neighbouring tiles.
+// Measured against 64x64 tiles of C staged through LDS, a workgroup each (M x N x K): 267 -> 9 us
+// (32x256x4098), 558 -> 21 (256x512x4098), 50 -> 4 (186x128x578), 20 -> 3 (32x256x256), gradients of
+// the weights 7.3 -> 4.4 (4098x256x32) and 41 -> 17 (4098x512x256).
+#define GT_ROWS 16
 #define GT_K 32
-#define GT_LDS 40   // bf16 per LDS row: 80 bytes, so every 8-element fragment is 16-byte aligned
 
-template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void k_gemm_bf16(int M, int N, int K, const float *__restrict__ A,
-                                                   int lda, const float *__restrict__ B, int ldb,
-                                                   float *__restrict__ C, int ldc,
-                                                   const float *__restrict__ bias,
-                                                   const float *__restrict__ gate, int relu,
-                                                   int accumulate)
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // any float's alignment
+
+// Eight values k .. k+7 of a row, contiguous (KC) or ld apart with TN adjacent ones each; those at
+// k >= K read the last value in range and are zero if GUARD
+template <bool KC, int TN, bool GUARD>
+__device__ __forceinline__ void gemm_load(const float *const (&p)[TN], size_t ld, int k, int K,
+                                          float (&v)[TN][8])
 {
-    __shared__ __attribute__((aligned(16))) __bf16 As[GT_M * GT_LDS];
-    __shared__ __attribute__((aligned(16))) __bf16 Bs[GT_N * GT_LDS];
-    const int m0 = blockIdx.y * GT_M, n0 = blockIdx.x * GT_N;
-    const int tid = threadIdx.x, wave = tid / DIGS_WAVE, lane = lane_id();
-    const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
-    f32x16 acc;
+    if constexpr (GUARD) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-    for (int k0 = 0; k0 < K; k0 += GT_K) {
-        for (int e = tid; e < GT_M * GT_K; e += 256) {
-            const int r = TA ? e % GT_M : e / GT_K, c = TA ? e / GT_M : e % GT_K;
-            const int m = m0 + r, k = k0 + c;
-            float v = 0.0f;
-            if (m < M && k < K) v = TA ? A[(size_t)k * lda + m] : A[(size_t)m * lda + k];
-            As[r * GT_LDS + c] = to_bf16(v);
-        }
-        for (int e = tid; e < GT_N * GT_K; e += 256) {
-            const int r = TB ? e / GT_K : e % GT_N, c = TB ? e % GT_K : e / GT_N;
-            const int nn = n0 + r, k = k0 + c;
-            float v = 0.0f;
-            if (nn < N && k < K) v = TB ? B[(size_t)nn * ldb + k] : B[(size_t)k * ldb + nn];
-            Bs[r * GT_LDS + c] = to_bf16(v);
-        }
-        __syncthreads();
+        for (int t = 0; t < TN; ++t)
 #pragma unroll
-        for (int s = 0; s < GT_K; s += 16) {
-            const int kk = s + 8 * (lane >> 5);
-            const bf16x8 a = *(const bf16x8 *)&As[(wm + (lane & 31)) * GT_LDS + kk];
-            const bf16x8 b = *(const bf16x8 *)&Bs[(wn + (lane & 31)) * GT_LDS + kk];
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    // result lane layout: element r of lane l is row 8(r/4) + 4(l/32) + r%4, column l%32
+            for (int j = 0; j < 8; ++j) {
+                const float x = p[t][(KC ? (size_t)1 : ld) * (size_t)min(k + j, K - 1)];
+                v[t][j] = k + j < K ? x : 0.0f;
+            }
+    } else if constexpr (KC) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int row = m0 + wm + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const int col = n0 + wn + (lane & 31);
-        if (row < M && col < N) {
-            const size_t o = (size_t)row * ldc + col;
-            float v = acc[r];
-            if (accumulate) v += C[o];
-            if (bias) v += bias[col];
-            if (relu) v = fmaxf(v, 0.0f);
-            if (gate && !(gate[o] > 0.0f)) v = 0.0f;
-            C[o] = v;
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+            for (int j = 0; j < 8; j += 4) {
+                const f32x4u x = *(const f32x4u *)(p[t] + k + j);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[t][j + i] = x[i];
+            }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float *q = p[0] + ld * (size_t)(k + j);
+            if constexpr (TN == 4) {
+                const f32x4u x = *(const f32x4u *)q;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) v[t][j] = x[t];
+            } else {
+                v[0][j] = *q;
+            }
         }
     }
 }
 
-// out[j] = sum_i X[i][j], rows summed in order (bias gradients)
-__global__ __launch_bounds__(256) void k_colsum(int M, int N, const float *__restrict__ X, int ldx,
-                                                float *__restrict__ out)
+__device__ __forceinline__ bf16x8 pack_bf16(const float (&v)[8])
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= N) return;
+    bf16x8 b;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) b[j] = (__bf16)v[j];   // rounds to nearest even
+    return b;
+}
+
+// Rows and columns beyond the matrix repeat its last ones and are not stored; TN == 4 needs N >= 4.
+template <bool TA, bool TB, int TN, int KW>
+__global__ __launch_bounds__(KW == 16 ? 1024 : 256) void k_gemm_bf16(
+    int M, int N, int K, const float *__restrict__ A, int lda, const float *__restrict__ B, int ldb,
+    float *__restrict__ C, int ldc, const float *__restrict__ bias,
+    const float *__restrict__ gate, int relu, int accumulate)
+{
+    constexpr int COLS = 16 * TN, NT = KW == 1 ? 4 : 1;   // tiles per workgroup
+    __shared__ __attribute__((aligned(16))) float red[KW == 1 ? 1 : KW * GT_ROWS * COLS];
+    const int wave = threadIdx.x / DIGS_WAVE, lane = lane_id();
+    const int ntn = (N + COLS - 1) / COLS, ntm = (M + GT_ROWS - 1) / GT_ROWS;
+    const int64_t tile = (int64_t)blockIdx.x * NT + (KW == 1 ? wave : 0);
+    const bool have = tile < (int64_t)ntn * ntm;   // (false only with KW == 1)
+    const int m0 = have ? (int)(tile / ntn) * GT_ROWS : 0, n0 = have ? (int)(tile % ntn) * COLS : 0;
+    const int kw = KW == 1 ? 0 : wave, kl = 8 * (lane >> 4);
+    const float *pa[1], *pb[TN];
+    const int row = min(m0 + (lane & 15), M - 1);
+    pa[0] = A + (TA ? (size_t)row : (size_t)row * lda);
+#pragma unroll
+    for (int t = 0; t < TN; ++t) {
+        const int col = min(n0 + TN * (lane & 15), N - TN) + t;
+        pb[t] = B + (TB ? (size_t)col * ldb : (size_t)col);
+    }
+    f32x4 acc[TN];
+#pragma unroll
+    for (int t = 0; t < TN; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto multiply = [&](const float (&a)[1][8], const float (&b)[TN][8]) {
+        const bf16x8 fa = pack_bf16(a[0]);
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, pack_bf16(b[t]), acc[t], 0, 0, 0);
+    };
+    const int steps = K / GT_K;
+    if (kw < steps) {
+        // the next step's operands are loaded before this one's are used
+        float a[1][8], b[TN][8], an[1][8], bn[TN][8];
+        gemm_load<!TA, 1, false>(pa, lda, kw * GT_K + kl, K, a);
+        gemm_load<TB, TN, false>(pb, ldb, kw * GT_K + kl, K, b);
+        for (int s = kw; s < steps; s += KW) {
+            const int k = min(s + KW, steps - 1) * GT_K + kl;
+            gemm_load<!TA, 1, false>(pa, lda, k, K, an);
+            gemm_load<TB, TN, false>(pb, ldb, k, K, bn);
+            multiply(a, b);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                a[0][j] = an[0][j];
+#pragma unroll
+                for (int t = 0; t < TN; ++t) b[t][j] = bn[t][j];
+            }
+        }
+    }
+    if (K % GT_K != 0 && kw == steps % KW) {
+        float a[1][8], b[TN][8];
+        gemm_load<!TA, 1, true>(pa, lda, steps * GT_K + kl, K, a);
+        gemm_load<TB, TN, true>(pb, ldb, steps * GT_K + kl, K, b);
+        multiply(a, b);
+    }
+    // row r of the tile and the TN columns of lane l % 16 == l
+    auto store = [&](int r, int l, const float (&v)[TN]) {
+        const int rw = m0 + r, first = n0 + TN * l, col = min(first, N - TN);
+        if (rw >= M || first >= N) return;
+        const size_t o = (size_t)rw * ldc + col;
+        float x[TN];
+#pragma unroll
+        for (int t = 0; t < TN; ++t) {
+            x[t] = v[t];
+            if (accumulate) x[t] += C[o + t];
+            if (bias) x[t] += bias[col + t];
+            if (relu) x[t] = fmaxf(x[t], 0.0f);
+            if (gate && !(gate[o + t] > 0.0f)) x[t] = 0.0f;
+        }
+        if (TN == 4 && first == col) {
+            *(f32x4u *)(C + o) = f32x4u{x[0], x[1 % TN], x[2 % TN], x[3 % TN]};
+        } else {   // (columns before `first` are another lane's)
+#pragma unroll
+            for (int t = 0; t < TN; ++t)
+                if (col + t >= first) C[o + t] = x[t];
+        }
+    };
+    // result lane layout: element r of lane l is row 4 (l / 16) + r, column l % 16
+    if constexpr (KW == 1) {
+        if (have)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float v[TN];
+#pragma unroll
+                for (int t = 0; t < TN; ++t) v[t] = acc[t][r];
+                store(4 * (lane >> 4) + r, lane & 15, v);
+            }
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int t = 0; t < TN; ++t)
+                red[(wave * GT_ROWS + 4 * (lane >> 4) + r) * COLS + TN * (lane & 15) + t] =
+                    acc[t][r];
+        __syncthreads();
+        if (threadIdx.x < 16 * GT_ROWS) {   // (row, lane of the row)
+            float v[TN];
+#pragma unroll
+            for (int t = 0; t < TN; ++t) {
+                const float *e = red + TN * threadIdx.x + t;
+                v[t] = e[0];
+#pragma unroll
+                for (int w = 1; w < KW; ++w) v[t] += e[w * GT_ROWS * COLS];
+            }
+            store(threadIdx.x >> 4, threadIdx.x & 15, v);
+        }
+    }
+}
+
+// out[j] = sum_i X[i][j] (bias gradients). A workgroup takes 64 columns, its 16 waves every 16th
+// row each, and their sums are added in wave order.
+#define COLSUM_WAVES 16
+__global__ __launch_bounds__(COLSUM_WAVES * DIGS_WAVE) void k_colsum(int M, int N,
+                                                                     const float *__restrict__ X,
+                                                                     int ldx,
+                                                                     float *__restrict__ out)
+{
+    __shared__ float part[COLSUM_WAVES][DIGS_WAVE];
+    const int wave = threadIdx.x / DIGS_WAVE, lane = lane_id();
+    const int64_t j = (int64_t)blockIdx.x * DIGS_WAVE + lane;
     float s = 0.0f;
-    for (int i = 0; i < M; ++i) s += X[(size_t)i * ldx + j];
-    out[j] = s;
+    if (j < N)
+#pragma unroll 4
+        for (int i = wave; i < M; i += COLSUM_WAVES) s += X[(size_t)i * ldx + j];
+    part[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && j < N) {
+#pragma unroll
+        for (int w = 1; w < COLSUM_WAVES; ++w) s += part[w][lane];
+        out[j] = s;
+    }
 }
 
 // Mean squared error against standardised targets, (pred - (target - mean)/std)^2 averaged over
@@ -242,6 +356,50 @@ __global__ __launch_bounds__(256) void k_lm_normal_eq(int T, int npix, const flo
 // ------------------------------------------------------------------------------------------
 static int wrc(hipError_t e) { return e == hipSuccess ? DIGS_OK : digs_set_hip_error(e); }
 
+struct GemmArgs {
+    int M, N, K;
+    const float *A;
+    int lda;
+    const float *B;
+    int ldb;
+    float *C;
+    int ldc;
+    const float *bias, *gate;
+    int relu, accumulate;
+    hipStream_t s;
+};
+
+template <bool TA, bool TB, int TN, int KW>
+static void launch_gemm_tiles(const GemmArgs &g, int64_t tiles)
+{
+    const int64_t wgs = KW == 1 ? (tiles + 3) / 4 : tiles;
+    hipLaunchKernelGGL((k_gemm_bf16<TA, TB, TN, KW>), dim3((unsigned)wgs),
+                       dim3((KW == 1 ? 4 : KW) * DIGS_WAVE), 0, g.s, g.M, g.N, g.K, g.A, g.lda, g.B,
+                       g.ldb, g.C, g.ldc, g.bias, g.gate, g.relu, g.accumulate);
+}
+
+// Waves over K, so that one has at most a few steps of 32 to take in turn: 16 from 1024 on, 4 from
+// 225 on. Wide tiles read A a quarter as often, but there are a quarter as many of them: they are
+// taken where that leaves two waves per SIMD (256x512x4098: 24 us narrow, 21 wide; 4098x512x256: 29
+// and 17), not below (32x256x4098: 9 us on 32 narrow tiles, 16 on 8 wide ones; 4098x256x32: 4.4 and
+// 5.5).
+template <bool TA, bool TB>
+static void launch_gemm(const GemmArgs &g)
+{
+    const int steps = (g.K + GT_K - 1) / GT_K, kw = steps >= 32 ? 16 : steps >= 8 ? 4 : 1;
+    const int64_t rows = (g.M + GT_ROWS - 1) / GT_ROWS;
+    const int64_t wide = rows * ((g.N + 63) / 64), narrow = rows * ((g.N + 15) / 16);
+    if (g.N >= 64 && wide * kw >= 2048) {
+        if (kw == 16) launch_gemm_tiles<TA, TB, 4, 16>(g, wide);
+        else if (kw == 4) launch_gemm_tiles<TA, TB, 4, 4>(g, wide);
+        else launch_gemm_tiles<TA, TB, 4, 1>(g, wide);
+    } else {
+        if (kw == 16) launch_gemm_tiles<TA, TB, 1, 16>(g, narrow);
+        else if (kw == 4) launch_gemm_tiles<TA, TB, 1, 4>(g, narrow);
+        else launch_gemm_tiles<TA, TB, 1, 1>(g, narrow);
+    }
+}
+
 extern "C" int digs_gemm_bf16(int M, int N, int K, const float *A, int lda, int transA,
                               const float *B, int ldb, int transB, float *C, int ldc,
                               const float *bias, const float *gate, int relu, int accumulate,
@@ -252,20 +410,11 @@ extern "C" int digs_gemm_bf16(int M, int N, int K, const float *A, int lda, int 
     if (M == 0 || N == 0) return DIGS_OK;
     if (!A || !B || !C || lda <= 0 || ldb <= 0 || ldc < N) return DIGS_EINVAL;
     if ((transA ? lda < M : lda < K) || (transB ? ldb < K : ldb < N)) return DIGS_EINVAL;
-    const dim3 grid((N + GT_N - 1) / GT_N, (M + GT_M - 1) / GT_M);
-    hipStream_t s = (hipStream_t)stream;
-    if (!transA && !transB)
-        hipLaunchKernelGGL((k_gemm_bf16<false, false>), grid, dim3(256), 0, s, M, N, K, A, lda,
-                           B, ldb, C, ldc, bias, gate, relu, accumulate);
-    else if (transA && !transB)
-        hipLaunchKernelGGL((k_gemm_bf16<true, false>), grid, dim3(256), 0, s, M, N, K, A, lda, B,
-                           ldb, C, ldc, bias, gate, relu, accumulate);
-    else if (!transA && transB)
-        hipLaunchKernelGGL((k_gemm_bf16<false, true>), grid, dim3(256), 0, s, M, N, K, A, lda, B,
-                           ldb, C, ldc, bias, gate, relu, accumulate);
-    else
-        hipLaunchKernelGGL((k_gemm_bf16<true, true>), grid, dim3(256), 0, s, M, N, K, A, lda, B,
-                           ldb, C, ldc, bias, gate, relu, accumulate);
+    GemmArgs g{M, N, K, A, lda, B, ldb, C, ldc, bias, gate, relu, accumulate, (hipStream_t)stream};
+    if (!transA && !transB) launch_gemm<false, false>(g);
+    else if (transA && !transB) launch_gemm<true, false>(g);
+    else if (!transA && transB) launch_gemm<false, true>(g);
+    else launch_gemm<true, true>(g);
     return wrc(hipGetLastError());
 }
 
@@ -273,8 +422,8 @@ extern "C" int digs_colsum(int M, int N, const float *X, int ldx, float *out, vo
 {
     if (M < 0 || N < 0 || (N > 0 && (!X || !out || ldx < N))) return DIGS_EINVAL;
     if (N == 0) return DIGS_OK;
-    hipLaunchKernelGGL(k_colsum, dim3((N + 255) / 256), dim3(256), 0, (hipStream_t)stream, M, N,
-                       X, ldx, out);
+    hipLaunchKernelGGL(k_colsum, dim3((N + DIGS_WAVE - 1) / DIGS_WAVE),
+                       dim3(COLSUM_WAVES * DIGS_WAVE), 0, (hipStream_t)stream, M, N, X, ldx, out);
     return wrc(hipGetLastError());
 }
 
