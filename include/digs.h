@@ -336,6 +336,9 @@ int digs_phi_grid(const digs_grid *grid, const float *coef, int n, const float *
  * digs_lm_normal_eq: imgs [T][R+1][npix] (base image, then the base with w_r raised by h[r]),
  *   meas [T][npix], h [R] (device) -> out [T][R(R+1)/2 + R + 1]: J^T J (upper triangle, row-major),
  *   J^T res, res.res with J_r = (I_r - I_0)/h_r, res = I_0 - P. Fixed-order sums.
+ * digs_lm_normal_eq_ws: the same on more of the chip, with the sums of slices of each view in ws
+ *   (4-byte aligned, digs_lm_workspace_size bytes; 0 for small views: ws may be null). The order of
+ *   the sums is fixed by npix.
  * digs_gemm_bf16: C[M][N] = A . B with A [M][K] (lda; transA: stored [K][M]) and B [K][N] (ldb;
  *   transB: stored [N][K]), FP32 in memory, BF16 operands on MFMA (v_mfma_f32_16x16x32_bf16), FP32
  *   accumulate; then, in order, + C if accumulate, + bias[N] if bias, max(., 0) if relu, 0 where
@@ -350,6 +353,9 @@ int digs_phi_grid(const digs_grid *grid, const float *coef, int n, const float *
  * Errors: DIGS_EINVAL, DIGS_EHIP. */
 int digs_lm_normal_eq(int T, int R, int npix, const float *imgs, const float *meas,
                       const float *h, float *out, void *stream);
+size_t digs_lm_workspace_size(int T, int R, int npix);
+int digs_lm_normal_eq_ws(int T, int R, int npix, const float *imgs, const float *meas,
+                         const float *h, float *out, void *ws, size_t ws_bytes, void *stream);
 int digs_gemm_bf16(int M, int N, int K, const float *A, int lda, int transA, const float *B,
                    int ldb, int transB, float *C, int ldc, const float *bias, const float *gate,
                    int relu, int accumulate, void *stream);

@@ -147,6 +147,9 @@ _SIGS = {
                                      _VP, _VP, ctypes.c_size_t, _VP]),
     "digs_lm_normal_eq": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_int, _VP, _VP, _VP,
                                          _VP, _VP]),
+    "digs_lm_workspace_size": (ctypes.c_size_t, [ctypes.c_int, ctypes.c_int, ctypes.c_int]),
+    "digs_lm_normal_eq_ws": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_int, _VP, _VP, _VP,
+                                            _VP, _VP, ctypes.c_size_t, _VP]),
     "digs_gemm_bf16": (ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_int, _VP, ctypes.c_int,
                                       ctypes.c_int, _VP, ctypes.c_int, ctypes.c_int, _VP,
                                       ctypes.c_int, _VP, _VP, ctypes.c_int, ctypes.c_int, _VP]),
@@ -654,9 +657,15 @@ def lm_normal_eq(imgs, meas, h, R: int, stream=None):
     """[T][R(R+1)/2 + R + 1] normal-equation terms from imgs [T][R+1][npix], meas [T][npix]."""
     T = meas.shape[0]
     npix = meas[0].numel() if T else 0
-    out = torch.empty((T, R * (R + 1) // 2 + R + 1), device=meas.device)
-    _check("digs_lm_normal_eq", load().digs_lm_normal_eq(T, R, npix, _ptr(imgs), _ptr(meas),
-                                                         _ptr(h), _ptr(out), _stream(stream)))
+    lib, n = load(), T * (R * (R + 1) // 2 + R + 1)
+    # the workspace follows the result in one allocation: it lives as long as the result does
+    # and, like it, belongs to whatever stream the caller runs this on
+    ws_bytes = lib.digs_lm_workspace_size(T, R, npix)
+    buf = torch.empty(n + ws_bytes // 4, device=meas.device)
+    out = buf[:n].view(T, n // T if T else R * (R + 1) // 2 + R + 1)
+    _check("digs_lm_normal_eq", lib.digs_lm_normal_eq_ws(
+        T, R, npix, _ptr(imgs), _ptr(meas), _ptr(h), _ptr(out), buf.data_ptr() + 4 * n, ws_bytes,
+        _stream(stream)))
     return out
 
 
