@@ -855,13 +855,6 @@ __device__ __forceinline__ void splat_fwd_cols(const float4 *__restrict__ rt,
     }
 }
 
-__device__ __forceinline__ void wave_sync_lds()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int B, int PATTERN>
 __device__ __forceinline__ void transpose_step(float (&v)[64], int lane)
 {

@@ -316,8 +316,9 @@ extern "C" int digs_dvf_grid(const digs_grid *grid, const float *coef, const flo
 
 // ------------------------------------------------------------------------------------------
 #define BRICK 8
+#define PHI_CHAIN 1.0f   // largest |r8| for the recurrence along z in k_phi_splat
 #define PHI_REC 12   // floats per Gaussian record: centre (3, voxel index units), exp2 quadratic
-                     // coefficients (6), rho, 2 unused
+                     // coefficients (6), rho, 2^(2 r8) or 0 (k_phi_splat), 1 unused
 
 struct PhiLayout {
     size_t diag, rec, brange, count, scratch, ka, va, kb, vb, rhist, bstart, total;
@@ -425,12 +426,13 @@ __global__ __launch_bounds__(256) void k_phi_setup(DevGrid g, const float *__res
     const int vn[3] = {v.nx, v.ny, v.nz};
     bool ok = isfinite(detK) && detK != 0.0f && s[0] > 0.0f && s[1] > 0.0f && s[2] > 0.0f &&
               isfinite(qn) && isfinite(rho[i]);
-    float c[3];
+    float c[3], hwv[3];
     int lo[3] = {1, 1, 1}, hi[3] = {0, 0, 0};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         c[a] = (mp[a] - vo[a]) / vs[a];
         const float hw = cull * sqrtf(fmaxf(Sd[a], 0.0f)) / vs[a];
+        hwv[a] = hw;
         ok = ok && isfinite(c[a]) && isfinite(hw);
         const float l = fminf(fmaxf(ceilf(c[a] - hw), -1.0f), (float)vn[a]);
         const float h = fminf(fmaxf(floorf(c[a] + hw), -1.0f), (float)vn[a]);
@@ -451,7 +453,11 @@ __global__ __launch_bounds__(256) void k_phi_setup(DevGrid g, const float *__res
     o[7] = any ? 2.0f * c2 * A[4] * vs[1] * vs[2] : 0.0f;
     o[8] = any ? c2 * A[5] * vs[2] * vs[2] : 0.0f;
     o[9] = any ? rho[i] : 0.0f;
-    o[10] = 0.0f;
+    // the recurrence of k_phi_splat: the ratio of its ratios, or 0 where it is not taken (a narrow
+    // Gaussian, or one whose ratios could leave the range of a float in a brick that it meets)
+    const float slope = fabsf(o[5]) * (hwv[0] + BRICK) + fabsf(o[7]) * (hwv[1] + BRICK) +
+                        fabsf(o[8]) * (2.0f * (hwv[2] + BRICK) + 1.0f);
+    o[10] = (o[8] >= -PHI_CHAIN && slope < 100.0f) ? __builtin_amdgcn_exp2f(2.0f * o[8]) : 0.0f;
     o[11] = 0.0f;
     uint32_t cnt = 0;
     int2 br = make_int2(1, 0);
@@ -517,38 +523,89 @@ __global__ void k_brick_start(int m, int nbricks, const uint32_t *__restrict__ k
     for (uint32_t k = lo; k <= hi; ++k) bstart[k] = (uint32_t)p;
 }
 
-// One workgroup per 8x8x8 brick: thread = (x, y, z and z + 4); the brick's Gaussians in order.
-__global__ __launch_bounds__(256) void k_phi_splat(DevVGrid v, int nbx, int nby,
-                                                   const float *__restrict__ rec,
-                                                   const uint32_t *__restrict__ vals,
-                                                   const uint32_t *__restrict__ bstart,
-                                                   size_t cap, float *__restrict__ phi)
+// One workgroup per 8x8x8 brick, its Gaussians split into four runs in order, one per wave; lane =
+// (x, y), a column of eight voxels each. A wave's Gaussians are staged in LDS 64 at a time, one
+// loaded by each lane, and read back by all lanes together; the waves' sums are added in order.
+//
+// VALU-bound. Along a column the exponent is quadratic with the Gaussian's own constant second
+// difference, so the values of four neighbouring voxels follow from two exponentials by a
+// recurrence of products, v(z+1) = v(z) r(z), r(z+1) = r(z) 2^(2 r8): 4.8 instruction slots per
+// voxel against 9 with an exponential each. It starts afresh every four voxels, and is taken only
+// where the coefficient r8 of the exponent along z is at most PHI_CHAIN (a deviation of 0.85 voxels
+// or more), so that the exponent at the start is at most 9 below that of the column's largest value
+// if that is among the four, and the products keep its relative rounding (six factors).
+// Measured with 500k Gaussians on 256^3 voxels, rank 4: 1915 -> 944 us; the whole call with 70k on
+// 78x70x64: 570 -> 201 us.
+#define PHI_WAVES 4
+
+__global__ __launch_bounds__(PHI_WAVES *DIGS_WAVE) void k_phi_splat(
+    DevVGrid v, int nbx, int nby, const float *__restrict__ rec, const uint32_t *__restrict__ vals,
+    const uint32_t *__restrict__ bstart, size_t cap, float *__restrict__ phi)
 {
+    __shared__ float4 stage[PHI_WAVES][DIGS_WAVE][PHI_REC / 4];
+    __shared__ float part[PHI_WAVES][BRICK][DIGS_WAVE];
     const int b = blockIdx.x;
     const int bx = b % nbx, by = (b / nbx) % nby, bz = b / (nbx * nby);
-    const int tx = threadIdx.x & 7, ty = (threadIdx.x >> 3) & 7, tz = threadIdx.x >> 6;
-    const int x = bx * BRICK + tx, y = by * BRICK + ty, z = bz * BRICK + tz;
-    const float fx = (float)x, fy = (float)y, fz0 = (float)z, fz1 = (float)(z + 4);
+    const int wave = uniform((int)(threadIdx.x / DIGS_WAVE)), lane = lane_id();
+    const float fx = (float)(bx * BRICK + (lane & 7)), fy = (float)(by * BRICK + (lane >> 3));
+    const float fz = (float)(bz * BRICK);
     uint32_t p0 = bstart[b], p1 = bstart[b + 1];
     p0 = (uint32_t)min((size_t)p0, cap);
     p1 = (uint32_t)min((size_t)max(p1, p0), cap);
-    float acc0 = 0.0f, acc1 = 0.0f;
-    for (uint32_t p = p0; p < p1; ++p) {
-        const uint32_t gi = uniform(vals[p]);
-        const float *r = rec + (size_t)gi * PHI_REC;
-        const float dx = fx - r[0], dy = fy - r[1];
-        const float qxy = fmaf(dx, fmaf(r[3], dx, r[4] * dy), r[6] * dy * dy);
-        const float lin = fmaf(r[5], dx, r[7] * dy);
-        const float dz0 = fz0 - r[2], dz1 = fz1 - r[2];
-        const float e0 = fmaf(dz0, fmaf(r[8], dz0, lin), qxy);
-        const float e1 = fmaf(dz1, fmaf(r[8], dz1, lin), qxy);
-        acc0 = fmaf(r[9], __builtin_amdgcn_exp2f(e0), acc0);
-        acc1 = fmaf(r[9], __builtin_amdgcn_exp2f(e1), acc1);
+    const uint32_t per = (p1 - p0 + PHI_WAVES - 1) / PHI_WAVES;
+    const uint32_t begin = min(p0 + per * (uint32_t)wave, p1), end = min(begin + per, p1);
+    float acc[BRICK];
+#pragma unroll
+    for (int k = 0; k < BRICK; ++k) acc[k] = 0.0f;
+    for (uint32_t c0 = begin; c0 < end; c0 += DIGS_WAVE) {
+        const uint32_t gi = vals[min(c0 + (uint32_t)lane, end - 1u)];
+        const float4 *r = (const float4 *)(rec + (size_t)gi * PHI_REC);
+#pragma unroll
+        for (int k = 0; k < PHI_REC / 4; ++k) stage[wave][lane][k] = r[k];
+        wave_sync_lds();
+        const int m = (int)min(end - c0, (uint32_t)DIGS_WAVE);
+        for (int j = 0; j < m; ++j) {
+            const float4 a = stage[wave][j][0], q = stage[wave][j][1], d = stage[wave][j][2];
+            const float dx = fx - a.x, dy = fy - a.y, dz = fz - a.z;
+            const float qxy = fmaf(dx, fmaf(a.w, dx, q.x * dy), q.z * dy * dy);
+            const float lin = fmaf(q.y, dx, q.w * dy);
+            if (d.z > 0.0f) {
+#pragma unroll
+                for (int k = 0; k < BRICK; k += 4) {
+                    const float z = dz + (float)k, s = fmaf(d.x, z, lin);
+                    float u = __builtin_amdgcn_exp2f(fmaf(z, s, qxy));
+                    float ratio = __builtin_amdgcn_exp2f(fmaf(d.x, z + 1.0f, s));
+                    acc[k] = fmaf(d.y, u, acc[k]);
+#pragma unroll
+                    for (int i = 1; i < 4; ++i) {
+                        u *= ratio;
+                        if (i < 3) ratio *= d.z;
+                        acc[k + i] = fmaf(d.y, u, acc[k + i]);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < BRICK; ++k) {
+                    const float z = dz + (float)k;
+                    const float e = fmaf(z, fmaf(d.x, z, lin), qxy);
+                    acc[k] = fmaf(d.y, __builtin_amdgcn_exp2f(e), acc[k]);
+                }
+            }
+        }
+        wave_sync_lds();
     }
+#pragma unroll
+    for (int k = 0; k < BRICK; ++k) part[wave][k][lane] = acc[k];
+    __syncthreads();
+    const int x = bx * BRICK + (lane & 7), y = by * BRICK + (lane >> 3);
     const size_t row = (size_t)v.ny * v.nx;
-    if (x < v.nx && y < v.ny) {
-        if (z < v.nz) phi[(size_t)z * row + (size_t)y * v.nx + x] = acc0;
-        if (z + 4 < v.nz) phi[(size_t)(z + 4) * row + (size_t)y * v.nx + x] = acc1;
+#pragma unroll
+    for (int k = wave; k < BRICK; k += PHI_WAVES) {
+        float s = part[0][k][lane];
+#pragma unroll
+        for (int w = 1; w < PHI_WAVES; ++w) s += part[w][k][lane];
+        const int z = bz * BRICK + k;
+        if (x < v.nx && y < v.ny && z < v.nz) phi[(size_t)z * row + (size_t)y * v.nx + x] = s;
     }
 }
 
