@@ -103,17 +103,18 @@ static int64_t default_capacity(int n, int T, int tile_px)
 // with 4 slices, 41 / 59 with 8, 45 / 65 with 16; 540 items of 20k Gaussians: 93 / 115, 57 / 80 with
 // 4, 62 / 94 with 12), at most 8 unless the lists are long: a slice for every 600 entries that a list
 // is expected to hold, at a dozen tiles per Gaussian (80 items of 103k Gaussians: 56 / 69 us with 8,
-// 45 / 56 with 16; 480 items of 58k on a 86x55 detector: 205 / 197 with 4, 178 / 181 with 8). With
+// 45 / 56 with 16; 480 items of 58k on a 86x55 detector: 171 / 194 with 4, 143 / 181 with 8). With
 // one to two resident rounds, long lists still gain by evening out the tiles (300k Gaussians,
-// 512x512, about 3500 entries a list: 156 / 263 -> 142 / 234 us with 3), short ones lose to the
-// partial images and their sum (80k: 76 / 140 -> 81 / 146): a slice for every thousand entries.
+// 512x512, about 3500 entries a list: 156 / 263 -> 142 / 234 us with 3; 1260 items of 2.4k Gaussians,
+// 1400 entries: 79 / 109 -> 69 / 101 with 2), short ones lose to the partial images and their sum
+// (80k: 83 / 143 -> 88 / 146): a slice for every 700 entries, rounded.
 static int default_slices(int64_t items, int n, int ntiles)
 {
     if (items >= 2048 || items <= 0) return 1;
     const int64_t most = std::min<int64_t>(DIGS_MAX_SLICES, (4096 + items - 1) / items);
     const int64_t entries = (int64_t)12 * n / ntiles;
     const int64_t s = items >= 1024
-                          ? std::max<int64_t>(1, entries / 1000)
+                          ? std::max<int64_t>(1, (entries + 300) / 700)
                           : std::max(std::min<int64_t>(8, (2048 + items - 1) / items),
                                      entries / 600);
     return (int)std::min(s, most);

@@ -705,18 +705,22 @@ __device__ __forceinline__ void slice_range(uint32_t &begin, uint32_t &end, int 
 // lane over its Gaussian's 64 pixels by the block polynomial (splat_poly.h) into 64 sums of its
 // own; those marked direct are set aside and evaluated by columns. The halves are evaluated at the
 // list's end, 32 pixels per Gaussian, their last partial group with the first queue's remainder. A
-// short remainder is evaluated by columns: lane = (Gaussian slot, column), eight Gaussians at a time, each lane down the rows of
-// its column by forward differences into 8 sums. The lanes' sums are added at the end in a fixed
-// order, and every pixel is written once.
+// short remainder is evaluated by columns: lane = (Gaussian slot, column), eight Gaussians at a
+// time, each lane down the rows of its column by forward differences into 8 sums. The lanes' sums
+// are added at the end in a fixed order, and every pixel is written once.
 //
 // VALU-bound. A lane per Gaussian makes the set-up of its polynomial (80 instructions) a 64-pixel
 // one and each pixel 2.5 multiply-adds, an exp2 and one more multiply-add: 430 instructions for 64
 // Gaussians' blocks, against 8 x 84 by columns (a reciprocal square root, an exp2 and seven others
 // per pixel). By the same count a remainder of up to FWD_COLS Gaussians is cheaper by columns.
 // Measured against columns for all of them: 4.72 -> 3.70 ms (200k Gaussians, 64 views of 512x384),
-// 5.75 -> 4.33 (500k, 16 views of 1024x768), 127 -> 93 us (80k, 512x512), EWA 787 -> 739 us (200k,
-// 16 views of 512x384). Without the queue of halves the first takes 3.80 ms. A block most of whose
-// Gaussians are direct stays with the columns (splat_fwd_tile).
+// 5.75 -> 4.33 (500k, 16 views of 1024x768), 127 -> 83 us (80k, 512x512). Without the queue of
+// halves the first takes 3.80 ms. A block many of whose Gaussians are direct stays with the columns
+// (splat_fwd_tile).
+//
+// The EWA model goes by columns throughout: a pixel there is an exp2 and three others already, and
+// the lanes' sums of a block cost more than they gain where lists are short (200k Gaussians, 16
+// views of 512x384: 734 us by columns, 739 by lanes; 2.3k, 62 views of 460x344: 310 and 396).
 #define FWD_QUEUE (2 * DIGS_WAVE)   // ring: fewer than 64 left over in each queue, and one chunk
 #define FWD_HALVES 512              // Gaussians that meet one half, kept to the list's end
 #define FWD_LDS (2 * FWD_QUEUE + FWD_HALVES)
@@ -747,7 +751,7 @@ __device__ __forceinline__ void add_pixel(float (&acc)[64], int r, int c, float 
 // (NROWS == 4) by the block polynomial. A queue entry is the byte offset of the Gaussian's record
 // and, in the low bits, the halves it meets (1 upper, 2 lower); with NROWS == 8 a half it does not
 // meet gets weight 0.
-template <bool EWA, int NROWS>
+template <int NROWS>
 __device__ __forceinline__ void splat_fwd_lanes(const float4 r0, const float4 r1, const float4 r2,
                                                 uint32_t ent, bool live, float bx, float by,
                                                 float (&acc)[64])
@@ -757,58 +761,31 @@ __device__ __forceinline__ void splat_fwd_lanes(const float4 r0, const float4 r1
     const float la = live ? r2.z : -INFINITY;   // (log2 0: adds zero)
     const float cx = bx + 3.5f;
     const float cy = (NROWS == 8 ? by : by + ((ent & 1u) ? 0.0f : 4.0f)) + 0.5f * (float)(NROWS - 1);
-    if constexpr (EWA) {
-        const float du = cx - r0.x, dv = cy - r0.y;
-        const float Huu = -fabsf(r0.z), mE = Huu * du, tE = fmaf(r0.w, dv, mE), nE = r1.x * dv;
-        const float E00 = fmaf(dv, nE, fmaf(du, tE, la)), E10 = tE + mE;
-        const float E01 = fmaf(r0.w, du, nE + nE);
+            BlockPoly b;
+            block_poly(r0, r1, r2, cx, cy, __ballot(mark_fold(r1)) != 0ull, b);
+            b.c[0] += la;
+            const float c40 = b.c[pidx(4, 0)];
 #pragma unroll
-        for (int rp = 0; rp < NROWS / 2; ++rp) {
-            const float t = (float)rp + 0.5f;
-            const float ev = fmaf(t * t, r1.x, E00);
+            for (int rp = 0; rp < NROWS / 2; ++rp) {
+                float k[2][4];
+                poly_rows(b.c, (float)rp + 0.5f, k);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const float k0 = fmaf(h == 0 ? t : -t, E01, ev);
-                const float k1 = fmaf(h == 0 ? t : -t, r0.w, E10);
-                const int r = h == 0 ? NROWS / 2 + rp : NROWS / 2 - 1 - rp;
+                for (int h = 0; h < 2; ++h) {
+                    const int r = h == 0 ? NROWS / 2 + rp : NROWS / 2 - 1 - rp;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const float s = (float)c + 0.5f, e = fmaf(s * s, Huu, k0);
-                    add_pixel<NROWS>(acc, r, 4 + c, __builtin_amdgcn_exp2f(fmaf(s, k1, e)), wu, wl);
-                    add_pixel<NROWS>(acc, r, 3 - c, __builtin_amdgcn_exp2f(fmaf(-s, k1, e)), wu,
-                                     wl);
+                    for (int c = 0; c < 4; ++c) {
+                        float xp, xm;
+                        poly_cols(k[h], c40, (float)c + 0.5f, xp, xm);
+                        add_pixel<NROWS>(acc, r, 4 + c, __builtin_amdgcn_exp2f(xp), wu, wl);
+                        add_pixel<NROWS>(acc, r, 3 - c, __builtin_amdgcn_exp2f(xm), wu, wl);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);   // (a row at a time: registers)
                 }
-                __builtin_amdgcn_sched_barrier(0);   // (a row at a time: registers)
             }
-        }
-    } else {
-        BlockPoly b;
-        block_poly(r0, r1, r2, cx, cy, __ballot(mark_fold(r1)) != 0ull, b);
-        b.c[0] += la;
-        const float c40 = b.c[pidx(4, 0)];
-#pragma unroll
-        for (int rp = 0; rp < NROWS / 2; ++rp) {
-            float k[2][4];
-            poly_rows(b.c, (float)rp + 0.5f, k);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int r = h == 0 ? NROWS / 2 + rp : NROWS / 2 - 1 - rp;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    float xp, xm;
-                    poly_cols(k[h], c40, (float)c + 0.5f, xp, xm);
-                    add_pixel<NROWS>(acc, r, 4 + c, __builtin_amdgcn_exp2f(xp), wu, wl);
-                    add_pixel<NROWS>(acc, r, 3 - c, __builtin_amdgcn_exp2f(xm), wu, wl);
-                }
-                __builtin_amdgcn_sched_barrier(0);   // (a row at a time: registers)
-            }
-        }
-    }
 }
 
 // Evaluates cnt queued Gaussians from position head of the queue q (mask: its size less one for a
 // ring, else ~0) by columns, eight at a time, into the 8 row sums of the lane's column.
-template <bool EWA>
 __device__ __forceinline__ void splat_fwd_cols(const float4 *__restrict__ rt,
                                                const uint32_t *__restrict__ q, int head, int cnt,
                                                int mask, int lane, float bx, float by,
@@ -827,30 +804,20 @@ __device__ __forceinline__ void splat_fwd_cols(const float4 *__restrict__ rt,
         const float AE = -fabsf(r0.z) * du * du, BE = r0.w * du, CE = r1.x;
         const float s1 = fmaf(2.0f, dv0, 1.0f);
         float e = fmaf(dv0, fmaf(CE, dv0, BE), AE), de = fmaf(CE, s1, BE);
-        if constexpr (EWA) {
-            e += la;   // amp 2^E = 2^(E + log2 amp)
+        // amp rs 2^x = rs 2^(x + log2 amp); q is kept positive where a half that the
+        // footprint does not meet carries weight 0
+        const float Aq = fmaf(du, fmaf(fabsf(r1.w), du, r1.y), 1.0f);
+        const float Bq = fmaf(r2.x, du, r1.z), Cq = fabsf(r2.y);
+        float qv = fmaf(dv0, fmaf(Cq, dv0, Bq), Aq), dq = fmaf(Cq, s1, Bq);
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                accc[r] = fmaf(r < 4 ? wu : wl, __builtin_amdgcn_exp2f(e), accc[r]);
-                e += de;
-                de += 2.0f * CE;
-            }
-        } else {
-            // amp rs 2^x = rs 2^(x + log2 amp); q is kept positive where a half that the
-            // footprint does not meet carries weight 0
-            const float Aq = fmaf(du, fmaf(fabsf(r1.w), du, r1.y), 1.0f);
-            const float Bq = fmaf(r2.x, du, r1.z), Cq = fabsf(r2.y);
-            float qv = fmaf(dv0, fmaf(Cq, dv0, Bq), Aq), dq = fmaf(Cq, s1, Bq);
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const float rs = __builtin_amdgcn_rsqf(fmaxf(qv, 1.0e-20f));
-                const float v = rs * __builtin_amdgcn_exp2f(fmaf(e, rs * rs, la));
-                accc[r] = fmaf(r < 4 ? wu : wl, v, accc[r]);
-                qv += dq;
-                dq += 2.0f * Cq;
-                e += de;
-                de += 2.0f * CE;
-            }
+        for (int r = 0; r < 8; ++r) {
+            const float rs = __builtin_amdgcn_rsqf(fmaxf(qv, 1.0e-20f));
+            const float v = rs * __builtin_amdgcn_exp2f(fmaf(e, rs * rs, la));
+            accc[r] = fmaf(r < 4 ? wu : wl, v, accc[r]);
+            qv += dq;
+            dq += 2.0f * Cq;
+            e += de;
+            de += 2.0f * CE;
         }
     }
 }
@@ -965,10 +932,12 @@ __device__ __forceinline__ void splat_cols_group(const float4 *__restrict__ rt,
 }
 
 // One wave's sums of its block at (bx, by) over list entries [begin, end), by columns throughout.
-// Three queues (LDS, FWD_COLS_QUEUE entries each): Gaussians that meet both halves of the block, only
-// the upper, only the lower; each is evaluated eight Gaussians at a time over the rows they meet, and
-// its remainder (fewer than 8) is carried over to the next chunk.
-#define FWD_COLS_QUEUE (DIGS_WAVE + 8)
+// Three queues in LDS (FWD_COLS_QUEUE entries each): Gaussians that meet both halves of the block,
+// only the upper, only the lower. They are filled from FWD_COLS_CHUNKS chunks of the list, whose
+// entries are loaded during the evaluation before; then each is evaluated eight Gaussians at a time
+// over the rows they meet, and its remainder (fewer than 8) is carried over.
+#define FWD_COLS_CHUNKS 3
+#define FWD_COLS_QUEUE (FWD_COLS_CHUNKS * DIGS_WAVE + 8)
 template <bool EWA>
 __device__ __forceinline__ float splat_cols_block(const float4 *__restrict__ rt,
                                                   const uint32_t *__restrict__ list,
@@ -981,30 +950,35 @@ __device__ __forceinline__ float splat_cols_block(const float4 *__restrict__ rt,
     float acc[8], accn[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) acc[r] = accn[r] = 0.0f;
-    // queued Gaussians carried over from earlier chunks (fewer than 8 per queue)
+    // queued Gaussians: carried over from earlier chunks, fewer than 8 per queue
     int pend0 = 0, pend1 = 0, pend2 = 0;
-    for (uint32_t c0 = begin; c0 < end; c0 += DIGS_WAVE) {
-        const uint32_t k = c0 + lane;
-        uint32_t g = 0, h = 0;
-        if (k < end) {
-            const uint32_t e = list[k];
-            g = e & LIST_INDEX_MASK;
-            h = g < (uint32_t)n ? (e >> (LIST_BLOCK_SHIFT + 2 * blkid)) & 3u : 0u;
+    uint32_t next[FWD_COLS_CHUNKS];
+#pragma unroll
+    for (int c = 0; c < FWD_COLS_CHUNKS; ++c)
+        next[c] = begin < end ? list[min(begin + DIGS_WAVE * c + lane, end - 1)] : 0u;
+    for (uint32_t c0 = begin; c0 < end; c0 += FWD_COLS_CHUNKS * DIGS_WAVE) {
+#pragma unroll
+        for (int c = 0; c < FWD_COLS_CHUNKS; ++c) {
+            const uint32_t k = c0 + DIGS_WAVE * c + lane, e = next[c], g = e & LIST_INDEX_MASK;
+            const uint32_t h = k < end && g < (uint32_t)n
+                                   ? (e >> (LIST_BLOCK_SHIFT + 2 * blkid)) & 3u : 0u;
+            next[c] = list[min(k + FWD_COLS_CHUNKS * DIGS_WAVE, end - 1)];
+            const unsigned long long m0 = __ballot(h == 3u), m1 = __ballot(h == 1u),
+                                     m2 = __ballot(h == 2u);
+            // a masked store per queue (the empty asm keeps the compiler from merging them
+            // into one store whose queue, count and mask each lane selects)
+            // (the queues hold the records' byte offsets, g * 64 < 2^30)
+            const uint32_t go = g << 6;
+            if (h == 3u) qs[0][pend0 + lane_rank(m0)] = go;
+            asm volatile("" ::: "memory");
+            if (h == 1u) qs[1][pend1 + lane_rank(m1)] = go;
+            asm volatile("" ::: "memory");
+            if (h == 2u) qs[2][pend2 + lane_rank(m2)] = go;
+            pend0 += __popcll(m0);
+            pend1 += __popcll(m1);
+            pend2 += __popcll(m2);
         }
-        const unsigned long long m0 = __ballot(h == 3u), m1 = __ballot(h == 1u),
-                                 m2 = __ballot(h == 2u);
-        // a masked store per queue (the empty asm keeps the compiler from merging them into
-        // one store whose queue, count and mask each lane selects)
-        // (the queues hold the records' byte offsets, g * 64 < 2^30)
-        const uint32_t go = g << 6;
-        if (h == 3u) qs[0][pend0 + lane_rank(m0)] = go;
-        asm volatile("" ::: "memory");
-        if (h == 1u) qs[1][pend1 + lane_rank(m1)] = go;
-        asm volatile("" ::: "memory");
-        if (h == 2u) qs[2][pend2 + lane_rank(m2)] = go;
-        const int ns0 = pend0 + __popcll(m0), ns1 = pend1 + __popcll(m1),
-                  ns2 = pend2 + __popcll(m2);
-        const int f0 = ns0 & ~7, f1 = ns1 & ~7, f2 = ns2 & ~7;
+        const int f0 = pend0 & ~7, f1 = pend1 & ~7, f2 = pend2 & ~7;
         wave_sync_lds();
         if (f0 > 0)
             splat_cols_group<EWA, 0, 8, false>(rt, qs[0], f0, gslot, fi, fby, acc, accn);
@@ -1016,16 +990,16 @@ __device__ __forceinline__ float splat_cols_block(const float4 *__restrict__ rt,
             // move each queue's remainder to its front: lane 8c + i moves entry i of queue c
             const int qc = lane >> 3, qi = lane & 7;
             const int fc = qc == 0 ? f0 : (qc == 1 ? f1 : f2);
-            const int lc = (qc == 0 ? ns0 : (qc == 1 ? ns1 : ns2)) - fc;
+            const int lc = (qc == 0 ? pend0 : (qc == 1 ? pend1 : pend2)) - fc;
             const bool mv = qc < 3 && qi < lc;
             const uint32_t keep = mv ? qs[qc][fc + qi] : 0u;
             wave_sync_lds();
             if (mv) qs[qc][qi] = keep;
             wave_sync_lds();
         }
-        pend0 = ns0 - f0;
-        pend1 = ns1 - f1;
-        pend2 = ns2 - f2;
+        pend0 -= f0;
+        pend1 -= f1;
+        pend2 -= f2;
     }
     if (pend0 > 0)
         splat_cols_group<EWA, 0, 8, true>(rt, qs[0], pend0, gslot, fi, fby, acc, accn);
@@ -1050,7 +1024,6 @@ __device__ __forceinline__ float splat_cols_block(const float4 *__restrict__ rt,
 
 // One wave's sums of its block at (bx, by) over list entries [begin, end): lane l returns pixel l.
 // next: the lane's entry of the first chunk (the last entry past the end).
-template <bool EWA>
 __device__ __forceinline__ float splat_fwd_block(const float4 *__restrict__ rt,
                                                  const uint32_t *__restrict__ list, uint32_t begin,
                                                  uint32_t end, int n, int blkid, int lane, int bx,
@@ -1088,8 +1061,8 @@ __device__ __forceinline__ float splat_fwd_block(const float4 *__restrict__ rt,
                 r2 = rg[2];
                 // Gaussians marked direct are set aside for the columns, or take the rest of
                 // their group with them if it would hold too few
-                const bool dir = !EWA && lane < c && mark_direct(r0);
-                const unsigned long long dm = EWA ? 0ull : __ballot(dir);
+                const bool dir = lane < c && mark_direct(r0);
+                const unsigned long long dm = __ballot(dir);
                 const bool cols = c - __popcll(dm) <= FWD_COLS;
                 live = lane < c && !dir;
                 if (!cols && dm != 0ull) {
@@ -1097,12 +1070,12 @@ __device__ __forceinline__ float splat_fwd_block(const float4 *__restrict__ rt,
                     n2 += __popcll(dm);
                     wave_sync_lds();
                     if (n2 >= DIGS_WAVE) {
-                        splat_fwd_cols<EWA>(rt, q2, 0, n2, ~0, lane, fx, fy, accc);
+                        splat_fwd_cols(rt, q2, 0, n2, ~0, lane, fx, fy, accc);
                         n2 = 0;
                     }
                 }
                 if (cols)
-                    splat_fwd_cols<EWA>(rt, q0, h0, c, FWD_QUEUE - 1, lane, fx, fy, accc);
+                    splat_fwd_cols(rt, q0, h0, c, FWD_QUEUE - 1, lane, fx, fy, accc);
                 h0 = (h0 + c) & (FWD_QUEUE - 1);
                 n0 -= c;
                 if (!cols) break;
@@ -1139,7 +1112,7 @@ __device__ __forceinline__ float splat_fwd_block(const float4 *__restrict__ rt,
             }
         }
         if (c == 0) break;
-        splat_fwd_lanes<EWA, 8>(r0, r1, r2, ent, live, fx, fy, acc);
+        splat_fwd_lanes<8>(r0, r1, r2, ent, live, fx, fy, acc);
         lanes = true;
     }
     // the full groups of halves
@@ -1152,15 +1125,15 @@ __device__ __forceinline__ float splat_fwd_block(const float4 *__restrict__ rt,
             r0 = rg[0];
             r1 = rg[1];
             r2 = rg[2];
-            if (EWA || __ballot(mark_direct(r0)) == 0ull) break;
-            splat_fwd_cols<EWA>(rt, q1, k, DIGS_WAVE, ~0, lane, fx, fy, accc);
+            if (__ballot(mark_direct(r0)) == 0ull) break;
+            splat_fwd_cols(rt, q1, k, DIGS_WAVE, ~0, lane, fx, fy, accc);
         }
         if (k >= n1) break;
         k += DIGS_WAVE;
-        splat_fwd_lanes<EWA, 4>(r0, r1, r2, ent, true, fx, fy, acc);
+        splat_fwd_lanes<4>(r0, r1, r2, ent, true, fx, fy, acc);
         lanes = true;
     }
-    if (n2 > 0) splat_fwd_cols<EWA>(rt, q2, 0, n2, ~0, lane, fx, fy, accc);
+    if (n2 > 0) splat_fwd_cols(rt, q2, 0, n2, ~0, lane, fx, fy, accc);
     wave_sync_lds();
     // the columns' sums over the 8 Gaussian slots (lane bits 3..5), then the lanes' sums
 #pragma unroll
@@ -1203,21 +1176,28 @@ __device__ __forceinline__ void splat_fwd_tile(const DevGeom &G, int n, int t, i
         const int blkid = WAVES > 1 ? wave : pass;
         const int bx = tx * G.tile_w + (blkid & (G.tile_bx - 1)) * 8;
         const int by = ty * G.tile_h + (blkid >> lbx) * 8;
-        // A block of whose first 64 entries more than 8 are marked direct goes by columns
-        // throughout: setting them aside costs more than the lanes gain (58k Gaussians, 20 views
-        // of 86x55 pixels of 4.5 mm, nearly all direct: 131 us by columns, 155 by this rule, 185
-        // without it; 200k on 1 mm pixels, nearly none: 4.72 ms by columns, 3.70 by this rule)
-        uint32_t first = LIST_INDEX_MASK;
-        if (begin < end) first = list[min(begin + lane, end - 1)];
-        bool cols = false;
-        if constexpr (!EWA) {
+        float v;
+        if constexpr (EWA) {
+            v = splat_cols_block<EWA>(rt, list, begin, end, n, blkid, lane, bx, by, ids[wave]);
+        } else {
+            // A block of whose first 64 entries more than 8 are marked direct goes by columns
+            // throughout: setting them aside costs more than the lanes gain (58k Gaussians, 20
+            // views of 86x55 pixels of 4.5 mm, nearly all direct: 144 us by this rule, 185 without
+            // it; 200k on 1 mm pixels, nearly none: 4.72 ms by columns, 3.70 by this rule)
+            uint32_t first = LIST_INDEX_MASK;
+            if (begin < end) first = list[min(begin + lane, end - 1)];
             const uint32_t g = first & LIST_INDEX_MASK;
             const float huu = g < (uint32_t)n ? rt[(size_t)g * 4].z : -1.0f;
-            cols = 8 * __popcll(__ballot(!signbit(huu))) > DIGS_WAVE;
+            if (8 * __popcll(__ballot(!signbit(huu))) > DIGS_WAVE) {
+                // (the empty asm keeps what the columns derive from the lane out of the registers
+                // of the other path, which has none to spare)
+                int l = lane;
+                asm volatile("" : "+v"(l));
+                v = splat_cols_block<EWA>(rt, list, begin, end, n, blkid, l, bx, by, ids[wave]);
+            } else {
+                v = splat_fwd_block(rt, list, begin, end, n, blkid, lane, bx, by, first, ids[wave]);
+            }
         }
-        float v;
-        if (cols) v = splat_cols_block<EWA>(rt, list, begin, end, n, blkid, lane, bx, by, ids[wave]);
-        else v = splat_fwd_block<EWA>(rt, list, begin, end, n, blkid, lane, bx, by, first, ids[wave]);
         const int px = bx + (lane & 7), py = by + (lane >> 3);
         if (nsl > 1) {
             const int p = (py - ty * G.tile_h) * G.tile_w + (px - tx * G.tile_w);
