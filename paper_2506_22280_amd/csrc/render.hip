@@ -2136,6 +2136,9 @@ __global__ __launch_bounds__(256, NR <= 3 ? 3 : 1) void k_tn_bwd(
     }
 }
 
+// added to the cell's x index in the sources of dL/dcoef of a Gaussian with a non-finite P or Q
+#define CG_BAD (1 << 20)
+
 template <int NR>
 __global__ __launch_bounds__(256) void k_gauss_reduce(
     DevGrid grid, int n, int nch, const float *__restrict__ coef, const float *__restrict__ gpar,
@@ -2273,7 +2276,15 @@ __global__ __launch_bounds__(256) void k_gauss_reduce(
     }
     // sources of dL/dcoef in cell order: clamped cell, fraction, P_r, Q_r
     float *o = gq + (size_t)i * gq_stride;
-    o[0] = __int_as_float(max(-2, min(st.fx, grid.nx + 1)));
+    bool finite = true;   // (k_coef_grad keeps a NaN or an infinity to the points it belongs to)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) finite = finite && isfinite(P[r][a]);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) finite = finite && isfinite(Q[r][k]);
+    }
+    o[0] = __int_as_float(max(-2, min(st.fx, grid.nx + 1)) + (finite ? 0 : CG_BAD));
     o[1] = __int_as_float(max(-2, min(st.fy, grid.ny + 1)));
     o[2] = __int_as_float(max(-2, min(st.fz, grid.nz + 1)));
     o[3] = inputs_ok ? st.px : 0.0f;
@@ -2282,9 +2293,11 @@ __global__ __launch_bounds__(256) void k_gauss_reduce(
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
 #pragma unroll
-        for (int a = 0; a < 3; ++a) o[6 + 12 * r + a] = P[r][a];
+        for (int a = 0; a < 3; ++a) {   // [P, Q_x, Q_y, Q_z][rank][component]
+            o[6 + 3 * r + a] = P[r][a];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) o[6 + 12 * r + 3 + k] = Q[r][k];
+            for (int c = 0; c < 3; ++c) o[6 + 3 * NR * (c + 1) + 3 * r + a] = Q[r][3 * a + c];
+        }
     }
 }
 
@@ -2345,30 +2358,83 @@ __global__ void k_cell_start(int n, int ncells, const uint32_t *__restrict__ key
     if (p < n) order[p] = min(vals[p], (uint32_t)(n - 1));
 }
 
-// One wave per control point: for each (cz, cy) row of its candidate cells the Gaussians of
-// the cells cx = lx..hx are contiguous in cell order; the lanes take the rows' Gaussians 64 at a
-// time over all rows together, and the per-lane sums are reduced over the wave in a fixed order.
-template <int NR>
-__global__ __launch_bounds__(256) void k_coef_grad(DevGrid g, const float *__restrict__ gq,
-                                                   int gq_stride,
-                                                   const uint32_t *__restrict__ cell_start,
-                                                   float *__restrict__ g_coef)
+// dL/dcoef: control point (i, j, k) of rank r gathers sum_p w0 P_r + w1 Q_r[0] + w2 Q_r[1] + w3 Q_r[2]
+// over the Gaussians p of its 4x4x4 cells, w0..w3 the products of its B-spline pieces at p and of
+// their x, y and z derivatives. For 16 control points (4 x 4 of one z) and the 3 NR components this
+// is a matrix product whose depth is four per Gaussian, v_mfma_f32_16x16x4_f32 in FP32.
+//
+// One workgroup per 4x4x1 control points. The Gaussians of its up to 8 x 8 x 5 cells are contiguous
+// per cell row; the waves take 64 of them in turn. Each lane lays one Gaussian's pieces at the
+// block's points into LDS, X and X' per column and Y Z, Y' Z, Y Z' per row, so that an operand is
+// one product of two words; P and Q are read from memory in the operand's layout. Four sums in turn
+// per wave, added over them and the waves in a fixed order.
+//
+// A wave per control point read every Gaussian 64 times, a lane each (168 bytes at R = 3, one cache
+// line per lane and load); a block reads it 12 times, coalesced. Blocks of a lattice plane go to one
+// XCD: neighbours in the plane share most of their Gaussians in its L2.
+// Measured against a wave per control point: 398 -> 171 us (200k Gaussians, 29^3 points, R = 3), 972
+// -> 287 (500k, 35^3, R = 4), 62 -> 40 (20k, 16^3), 72 -> 61 (80k, 29^3, R = 2). The products are a
+// third of the time, the pieces and the addresses most of the rest; the fullest block holds seven
+// times the mean.
+#define CG_TAB 20                 // floats per Gaussian: X[4], X'[4], YZ[4], Y'Z[4], YZ'[4]
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // any float's alignment
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+
+// The pieces b and their derivatives db of a Gaussian in cell c at the lattice points p0 .. p0+3 of
+// an axis of n points. Points beyond the lattice's ends count for the end: end tells (for the whole
+// wave) that the four reach one; elsewhere the pieces are only shifted.
+__device__ __forceinline__ void block_pieces(const float b[4], const float db[4], int c, int p0,
+                                             int n, bool end, float v[4], float dv[4])
 {
-    const int idx = blockIdx.x * 4 + threadIdx.x / DIGS_WAVE;
-    const int lane = lane_id();
-    const int npts = g.nx * g.ny * g.nz;
-    if (idx >= npts) return;
-    const int i = idx % g.nx, j = (idx / g.nx) % g.ny, k = idx / (g.nx * g.ny);
-    float acc[NR][3];
+    const int d = c - 1 - p0;
 #pragma unroll
-    for (int r = 0; r < NR; ++r) acc[r][0] = acc[r][1] = acc[r][2] = 0.0f;
-    const int lx = (i == 0) ? -2 : i - 2, hx = (i == g.nx - 1) ? g.nx + 1 : i + 1;
-    const int ly = (j == 0) ? -2 : j - 2, hy = (j == g.ny - 1) ? g.ny + 1 : j + 1;
+    for (int m = 0; m < 4; ++m) v[m] = dv[m] = 0.0f;
+    if (end) {
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            const int q = clampi(c - 1 + l, n) - p0;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                v[m] += q == m ? b[l] : 0.0f;
+                dv[m] += q == m ? db[l] : 0.0f;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int s = -3; s <= 3; ++s) {
+            const bool here = d == s;
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                if (m - s >= 0 && m - s < 4) {
+                    v[m] = here ? b[m - s] : v[m];
+                    dv[m] = here ? db[m - s] : dv[m];
+                }
+        }
+    }
+}
+
+template <int NR, int WAVES>
+__global__ __launch_bounds__(WAVES *DIGS_WAVE) void k_coef_grad(
+    DevGrid g, const float *__restrict__ gq, int gq_stride,
+    const uint32_t *__restrict__ cell_start, float *__restrict__ g_coef)
+{
+    constexpr int NT = (3 * NR + 15) / 16;   // column tiles
+    __shared__ __attribute__((aligned(16))) float tab[WAVES][DIGS_WAVE][CG_TAB];
+    static_assert(NT * 4 <= CG_TAB, "the waves' sums take the tables' place");
+    const int nbx = (g.nx + 3) >> 2, nby = (g.ny + 3) >> 2, plane = nbx * nby;
+    const int xcd = blockIdx.x & 7, b = blockIdx.x >> 3;
+    const int k = (b / plane) * 8 + xcd;
+    if (k >= g.nz) return;
+    const int i0 = (b % plane) % nbx * 4, j0 = (b % plane) / nbx * 4;
+    const int i1 = min(i0 + 3, g.nx - 1), j1 = min(j0 + 3, g.ny - 1);
+    const int wave = uniform((int)(threadIdx.x / DIGS_WAVE)), lane = lane_id();
+    const int lx = (i0 == 0) ? -2 : i0 - 2, hx = (i1 == g.nx - 1) ? g.nx + 1 : i1 + 1;
+    const int ly = (j0 == 0) ? -2 : j0 - 2, hy = (j1 == g.ny - 1) ? g.ny + 1 : j1 + 1;
     const int lz = (k == 0) ? -2 : k - 2, hz = (k == g.nz - 1) ? g.nz + 1 : k + 1;
     const float ihx = 1.0f / g.hx, ihy = 1.0f / g.hy, ihz = 1.0f / g.hz;
-    // The support's cell rows (cz, cy), at most 5 x 5, each a contiguous range of Gaussians in
-    // cell order: lane r < nrows holds row r's range, and the rows' Gaussians are taken 64 at a
-    // time over all rows together (a row holds only a few Gaussians).
+    // lane r < nrows holds cell row r's range of Gaussians (at most 8 x 5 rows)
     const int nry = hy - ly + 1, nrows = (hz - lz + 1) * nry;
     uint32_t rb = 0, rlen = 0;
     if (lane < nrows) {
@@ -2377,63 +2443,177 @@ __global__ __launch_bounds__(256) void k_coef_grad(DevGrid g, const float *__res
         rb = cell_start[row + (lx + 2)];
         rlen = cell_start[row + (hx + 2) + 1] - rb;
     }
-    // inclusive prefix sum of the row lengths over lanes 0..31 (nrows <= 25)
     uint32_t incl = rlen;
 #pragma unroll
-    for (int off = 1; off < 32; off <<= 1) {
+    for (int off = 1; off < DIGS_WAVE; off <<= 1) {
         const uint32_t y = __shfl_up(incl, off, DIGS_WAVE);
         if (lane >= off) incl += y;
     }
-    const uint32_t total = __shfl(incl, 31, DIGS_WAVE);
-    for (uint32_t q0 = 0; q0 < total; q0 += DIGS_WAVE) {
-        // the row of flattened index q: the first lane whose inclusive sum exceeds q (the
-        // shuffles run with every lane active; lanes past the end then skip the work)
-        const uint32_t q = q0 + (uint32_t)lane;
+    const uint32_t total = __shfl(incl, DIGS_WAVE - 1, DIGS_WAVE);
+    // operand A: row = point (i = lane % 4, j = lane / 4 % 4), depth c = lane / 16; operand B: depth
+    // c, column = component lane % 16 (+ 16)
+    const int c = lane >> 4, col = lane & 15;
+    const int xo = (c == 1 ? 4 : 0) + (lane & 3);
+    const int yo = 8 + (c == 2 ? 4 : (c == 3 ? 8 : 0)) + ((lane >> 2) & 3);
+    const uint32_t row_bytes = (uint32_t)gq_stride * 4u;
+    uint32_t so[NT];
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {   // (a column past the components repeats the last)
+        so[u] = (uint32_t)(6 + 3 * NR * c + min(16 * u + col, 3 * NR - 1));
+    }
+    f32x4 acc[NT][4];
+#pragma unroll
+    for (int u = 0; u < NT; ++u)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) acc[u][m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // the lane's Gaussian of the wave's 64 from q0: of flattened index q, in the first row whose
+    // inclusive sum exceeds q (past the end the last Gaussian again)
+    const auto position = [&](uint32_t q0) {
+        const uint32_t q = min(q0 + (uint32_t)lane, total - 1u);
         int row = 0;
 #pragma unroll
-        for (int step = 16; step >= 1; step >>= 1)
+        for (int step = DIGS_WAVE / 2; step >= 1; step >>= 1)
             if (__shfl(incl, row + step - 1, DIGS_WAVE) <= q) row += step;
-        row = min(row, 31);
-        const uint32_t p = __shfl(rb, row, DIGS_WAVE) + q -
-                           (__shfl(incl, row, DIGS_WAVE) - __shfl(rlen, row, DIGS_WAVE));
-        if (q >= total) continue;
-        const float *o = gq + (size_t)p * gq_stride;
-        // the Gaussian's (clamped) cell
-        const int cx = __float_as_int(o[0]), cy = __float_as_int(o[1]), cz = __float_as_int(o[2]);
-        float B[4], dB[4];
-        float wx = 0.f, dwx = 0.f, wy = 0.f, dwy = 0.f, wz = 0.f, dwz = 0.f;
-        bspline4(o[3], B);
-        bspline4_d(o[3], dB);
+        return __shfl(rb, row, DIGS_WAVE) + q -
+               (__shfl(incl, row, DIGS_WAVE) - __shfl(rlen, row, DIGS_WAVE));
+    };
+    uint32_t pnext = 0;
+    float on[6];
+    const auto fetch = [&](uint32_t q0) {
+        pnext = position(q0);
+        const float *o = gq + (size_t)pnext * gq_stride;
+        const f32x4u a = *(const f32x4u *)o;
+        const f32x2u b = *(const f32x2u *)(o + 4);
 #pragma unroll
-        for (int l = 0; l < 4; ++l)
-            if (clampi(cx - 1 + l, g.nx) == i) { wx += B[l]; dwx += dB[l]; }
-        bspline4(o[4], B);
-        bspline4_d(o[4], dB);
+        for (int e = 0; e < 6; ++e) on[e] = e < 4 ? a[e & 3] : b[e & 1];
+    };
+    if (wave * DIGS_WAVE < total) fetch(wave * DIGS_WAVE);
+    for (uint32_t q0 = wave * DIGS_WAVE; q0 < total; q0 += WAVES * DIGS_WAVE) {
+        const int cnt = (int)min(total - q0, (uint32_t)DIGS_WAVE);
+        const uint32_t p = pnext;
+        int cx = __float_as_int(on[0]);
+        const int cy = __float_as_int(on[1]), cz = __float_as_int(on[2]);
+        const float ux = on[3], uy = on[4], uz = on[5];
+        // (operands are on their way during the products before: P and Q of the next eight in one
+        // of two buffers, and the wave's next Gaussians)
+        const auto load8 = [&](int m0, float(&sv)[NT][8]) {
 #pragma unroll
-        for (int l = 0; l < 4; ++l)
-            if (clampi(cy - 1 + l, g.ny) == j) { wy += B[l]; dwy += dB[l]; }
-        bspline4(o[5], B);
-        bspline4_d(o[5], dB);
+            for (int m = 0; m < 8; ++m) {
+                const uint32_t pm = (uint32_t)__builtin_amdgcn_readlane((int)p, m0 + m);
+                const float *S = (const float *)((const char *)gq + (uint64_t)pm * row_bytes);
 #pragma unroll
-        for (int l = 0; l < 4; ++l)
-            if (clampi(cz - 1 + l, g.nz) == k) { wz += B[l]; dwz += dB[l]; }
-        const float w0 = wx * wy * wz, w1 = dwx * ihx * wy * wz, w2 = wx * dwy * ihy * wz,
-                    w3 = wx * wy * dwz * ihz;
+                for (int u = 0; u < NT; ++u) sv[u][m] = S[so[u]];
+            }
+        };
+        float s0[NT][8], s1[NT][8];
+        load8(0, s0);
+        fetch(min(q0 + WAVES * DIGS_WAVE, total - 1u));
+        const bool bad = cx > CG_BAD / 2;
+        cx -= bad ? CG_BAD : 0;
+        float B[4], dB[4], x[4], dx[4], y[4], dy[4];
+        bspline4(uz, B);
+        bspline4_d(uz, dB);
+        float wz = 0.0f, dwz = 0.0f;
+        if (k == 0 || k == g.nz - 1) {
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const float *Pr = o + 6 + 12 * r, *Qr = Pr + 3;
+            for (int l = 0; l < 4; ++l) {
+                const bool here = clampi(cz - 1 + l, g.nz) == k;
+                wz += here ? B[l] : 0.0f;
+                dwz += here ? dB[l] : 0.0f;
+            }
+        } else {
 #pragma unroll
-            for (int a = 0; a < 3; ++a)
-                acc[r][a] += w0 * Pr[a] + w1 * Qr[3 * a] + w2 * Qr[3 * a + 1] + w3 * Qr[3 * a + 2];
+            for (int l = 0; l < 4; ++l) {
+                const bool here = cz - 1 + l == k;
+                wz = here ? B[l] : wz;
+                dwz = here ? dB[l] : dwz;
+            }
         }
+        wz = lane < cnt ? wz : 0.0f;
+        dwz = lane < cnt ? dwz * ihz : 0.0f;
+        float4 *tb = (float4 *)tab[wave][lane];
+        bspline4(ux, B);
+        bspline4_d(ux, dB);
+        block_pieces(B, dB, cx, i0, g.nx, i0 == 0 || i1 == g.nx - 1, x, dx);
+        tb[0] = make_float4(x[0], x[1], x[2], x[3]);
+        tb[1] = make_float4(dx[0] * ihx, dx[1] * ihx, dx[2] * ihx, dx[3] * ihx);
+        bspline4(uy, B);
+        bspline4_d(uy, dB);
+        block_pieces(B, dB, cy, j0, g.ny, j0 == 0 || j1 == g.ny - 1, y, dy);
+        const float wyz = ihy * wz;
+        tb[2] = make_float4(y[0] * wz, y[1] * wz, y[2] * wz, y[3] * wz);
+        tb[3] = make_float4(dy[0] * wyz, dy[1] * wyz, dy[2] * wyz, dy[3] * wyz);
+        tb[4] = make_float4(y[0] * dwz, y[1] * dwz, y[2] * dwz, y[3] * dwz);
+        wave_sync_lds();
+        const float(*tw)[CG_TAB] = tab[wave];
+        if (__ballot(bad) == 0ull) {
+            float x0[8], y0[8], x1[8], y1[8];
+            const auto weights8 = [&](int m0, float(&xw)[8], float(&yw)[8]) {
+#pragma unroll
+                for (int m = 0; m < 8; ++m) {
+                    xw[m] = tw[m0 + m][xo];
+                    yw[m] = tw[m0 + m][yo];
+                }
+                __builtin_amdgcn_sched_barrier(0);   // (all on their way before the products)
+            };
+            const auto multiply8 = [&](const float(&sv)[NT][8], const float(&xw)[8],
+                                       const float(&yw)[8]) {
+#pragma unroll
+                for (int m = 0; m < 8; ++m)
+#pragma unroll
+                    for (int u = 0; u < NT; ++u)
+                        acc[u][m & 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                            xw[m] * yw[m], sv[u][m], acc[u][m & 3], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            weights8(0, x0, y0);
+            for (int m0 = 0; m0 < cnt; m0 += 16) {
+                load8(m0 + 8, s1);
+                weights8(m0 + 8, x1, y1);
+                multiply8(s0, x0, y0);
+                load8(min(m0 + 16, DIGS_WAVE - 8), s0);
+                weights8(min(m0 + 16, DIGS_WAVE - 8), x0, y0);
+                multiply8(s1, x1, y1);
+            }
+        } else {
+            // A product with a zero weight would carry a NaN or an infinity to points that the
+            // Gaussian does not reach: each sum by itself, only where it has a weight
+            for (int m = 0; m < cnt; ++m) {
+                const uint32_t pm = (uint32_t)__builtin_amdgcn_readlane((int)p, m);
+#pragma unroll
+                for (int u = 0; u < NT; ++u) {
+                    const float *S = gq + (size_t)pm * gq_stride + 6 + min(16 * u + col, 3 * NR - 1);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float X = tw[m][i], dX = tw[m][4 + i], Y = tw[m][8 + c],
+                                    dY = tw[m][12 + c], dZ = tw[m][16 + c];
+                        if ((X != 0.0f || dX != 0.0f) && (Y != 0.0f || dY != 0.0f || dZ != 0.0f))
+                            acc[u][0][i] += X * Y * S[0] + dX * Y * S[3 * NR] +
+                                            X * dY * S[6 * NR] + X * dZ * S[9 * NR];
+                    }
+                }
+            }
+        }
+        wave_sync_lds();
     }
+    // result lane layout: element i of lane l is row 4 (l / 16) + i (point i, j = l / 16), column l % 16
+    float(*red)[NT][4][DIGS_WAVE] = (float(*)[NT][4][DIGS_WAVE])tab;
+    __syncthreads();   // (every wave is done with its table)
 #pragma unroll
-    for (int r = 0; r < NR; ++r)
+    for (int u = 0; u < NT; ++u)
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const float v = wave_sum(acc[r][a]);
-            if (lane == 0) g_coef[((size_t)r * npts + idx) * 3 + a] = v;
-        }
+        for (int i = 0; i < 4; ++i)
+            red[wave][u][i][lane] = (acc[u][0][i] + acc[u][1][i]) + (acc[u][2][i] + acc[u][3][i]);
+    __syncthreads();
+    for (int e = threadIdx.x; e < NT * 4 * DIGS_WAVE; e += WAVES * DIGS_WAVE) {
+        const int l = e & 63, i = (e >> 6) & 3, u = e >> 8;
+        float s = red[0][u][i][l];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) s += red[w][u][i][l];
+        const int n = 16 * u + (l & 15), x = i0 + i, y = j0 + (l >> 4);
+        if (n < 3 * NR && x < g.nx && y < g.ny)
+            g_coef[((((size_t)(n / 3) * g.nz + k) * g.ny + y) * g.nx + x) * 3 + n % 3] = s;
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2722,8 +2902,18 @@ static hipError_t backward_dispatch(const RenderArgs &a, float *g_mu, float *g_s
     if (e != hipSuccess || a.basis) return e;   // (a per-Gaussian basis has no lattice gather)
     {
         ProfScope ps(PS_COEF_GRAD, s);
-        const int npts = a.grid.nx * a.grid.ny * a.grid.nz;
-        hipLaunchKernelGGL(k_coef_grad<NR>, dim3((npts + 3) / 4), dim3(256), 0, s, a.grid,
+        const int plane = ((a.grid.nx + 3) / 4) * ((a.grid.ny + 3) / 4);
+        const dim3 blocks((a.grid.nz + 7) / 8 * 8 * plane);
+        // Waves per block: 16 where there are fewer than a thousand blocks, so that the fullest is
+        // done sooner (20k Gaussians, 16^3 points, 256 blocks: 46 us with 8, 40 with 16), else 8, so
+        // that a CU holds several blocks at different stages. Two column tiles leave registers for
+        // 8 only.
+        if (NR <= 5 && plane * a.grid.nz < 1000)
+            hipLaunchKernelGGL((k_coef_grad<NR, (NR <= 5 ? 16 : 8)>), blocks, dim3(1024), 0, s, a.grid,
+                           WS(a, gq, const float *), a.L.gq_stride,
+                           WS(a, cell_start, const uint32_t *), g_coef);
+        else
+            hipLaunchKernelGGL((k_coef_grad<NR, 8>), blocks, dim3(512), 0, s, a.grid,
                            WS(a, gq, const float *), a.L.gq_stride,
                            WS(a, cell_start, const uint32_t *), g_coef);
         e = hipGetLastError();
