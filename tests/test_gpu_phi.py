@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from gpu_helpers import dev
 from paper_2506_22280_amd import _lib, synth
 
@@ -57,3 +58,27 @@ def _factor(scale, quat):
                   [2 * (x * y + w * z), 1 - 2 * (x * x + z * z), 2 * (y * z - w * x)],
                   [2 * (x * z - w * y), 2 * (y * z + w * x), 1 - 2 * (x * x + y * y)]])
     return R * scale.astype(np.float64)
+
+
+@pytest.mark.parametrize("R", [1, 3, 8])
+def test_phi_lattice_combined_or_not(R):
+    """The ranks combined once per lattice point, or per Gaussian where the workspace is too small for
+    that: both against the oracle's warp. Bar: the suite's for volumes."""
+    print("case: phi, rank %d, combined lattice and not" % R, flush=True)
+    p = synth.lung_phantom("phi", 40, 32, 32, 8.0, 2, min(R, 3), 25.0, 3)
+    p.grid["R"], p.coef = R, np.concatenate([p.coef] * 3)[:R]   # (the phantom has few modes)
+    v = dict(nx=21, ny=19, nz=23, origin=[-100.0, -90.0, -110.0], spacing=[10.0] * 3)
+    w = np.random.default_rng(R).normal(0, 0.5, R).astype(np.float32)
+    mu_t, cov_t = oracle.deform(p.grid, p.coef, p.mu, p.scale, p.quat, w[None])
+    z, y, x = np.meshgrid(*[np.arange(v[k]) for k in ("nz", "ny", "nx")], indexing="ij")
+    pts = np.stack([v["origin"][a] + 10.0 * q.ravel() for a, q in enumerate((x, y, z))])
+    ref = oracle.phi(mu_t[0], cov_t[0], p.rho, pts)
+    args = (p.grid, dev(p.coef), dev(p.mu), dev(p.scale), dev(p.quat), dev(p.rho), dev(w), v)
+    ws = _lib.Workspace()
+    got = [_lib.phi_grid(*args, ws, capacity=c, grow=False).cpu().numpy().ravel()
+           for c in (40 * 27, 1 << 16)]
+    points = p.grid["nx"] * p.grid["ny"] * p.grid["nz"]
+    assert 40 * 27 * 8 + 512 < 16 * points <= (1 << 16) * 8, points
+    assert ws.diagnostics()["instances"] <= 40 * 27
+    for g in got:
+        assert np.abs(g - ref).max() <= 1e-4 * np.abs(ref).max()
