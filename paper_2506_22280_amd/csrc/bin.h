@@ -43,7 +43,8 @@ __device__ __forceinline__ unsigned long long wave_match(unsigned key, bool acti
 
 // (a wave takes ITEMS / BIN_WAVES items, each with at most one instance of a key, so the offsets
 // of waves 1-3 within a block, at most 3 ITEMS / BIN_WAVES, fit 10 bits each)
-template <class Src, int ITEMS>
+// SELF: one slice of 256 keys, whose counts are laid out by block instead, for k_bin_fill to sum
+template <class Src, int ITEMS, bool SELF>
 __global__ __launch_bounds__(BIN_THREADS) void k_bin_count(Src src, uint32_t *__restrict__ cnt,
                                                            uint32_t *__restrict__ pre, int nbins,
                                                            int nblk)
@@ -65,14 +66,17 @@ __global__ __launch_bounds__(BIN_THREADS) void k_bin_count(Src src, uint32_t *__
     for (int b = threadIdx.x; b < nbins; b += BIN_THREADS) {
         const uint32_t c0 = hist[b], c1 = hist[nbins + b], c2 = hist[2 * nbins + b];
         const uint32_t c3 = hist[3 * nbins + b];
-        cnt[((size_t)slice * nbins + b) * nblk + blk] = c0 + c1 + c2 + c3;
+        cnt[SELF ? (size_t)blk * nbins + b : ((size_t)slice * nbins + b) * nblk + blk] =
+            c0 + c1 + c2 + c3;
         // (the offsets in workgroup-major order: each workgroup writes, and reads, one run)
         pre[((size_t)slice * nblk + blk) * nbins + b] =
             c0 | ((c0 + c1) << 10) | ((c0 + c1 + c2) << 20);
     }
 }
 
-template <class Src, int ITEMS>
+// SELF: cnt_scan holds the counts as they are, [block][256]; thread d adds up those of key d, in
+// all blocks and in the ones before this, and the workgroup scans the totals.
+template <class Src, int ITEMS, bool SELF>
 __global__ __launch_bounds__(BIN_THREADS) void k_bin_fill(Src src,
                                                           const uint32_t *__restrict__ cnt_scan,
                                                           const uint32_t *__restrict__ pre,
@@ -84,9 +88,33 @@ __global__ __launch_bounds__(BIN_THREADS) void k_bin_fill(Src src,
     uint32_t *h = hist + wave * nbins;
     constexpr int PER_WAVE = ITEMS / BIN_WAVES;
     const int base = blk * ITEMS + wave * PER_WAVE;
+    if (slice == 0 && blk == 0 && threadIdx.x == 0) src.begin_fill();
+    uint32_t self = 0;
+    if constexpr (SELF) {
+        __shared__ uint32_t wave_total[BIN_WAVES];
+        uint32_t total = 0;
+#pragma unroll 8
+        for (int b = 0; b < nblk; ++b) {
+            const uint32_t c = cnt_scan[(size_t)b * BIN_THREADS + threadIdx.x];
+            total += c;
+            self += b < blk ? c : 0u;
+        }
+        uint32_t incl = total;
+#pragma unroll
+        for (int off = 1; off < DIGS_WAVE; off <<= 1) {
+            const uint32_t y = __shfl_up(incl, off, DIGS_WAVE);
+            if (lane >= off) incl += y;
+        }
+        if (lane == DIGS_WAVE - 1) wave_total[wave] = incl;
+        __syncthreads();
+        self += incl - total;
+#pragma unroll
+        for (int w = 0; w < BIN_WAVES; ++w) self += w < wave ? wave_total[w] : 0u;
+    }
     // each wave's first position per key: the block's (scanned) plus the wave's offset within it
     for (int b = threadIdx.x; b < nbins; b += BIN_THREADS) {
-        const uint32_t run = cnt_scan[((size_t)slice * nbins + b) * nblk + blk];
+        const uint32_t run =
+            SELF ? self : cnt_scan[((size_t)slice * nbins + b) * nblk + blk];
         const uint32_t p = pre[((size_t)slice * nblk + blk) * nbins + b];
         hist[b] = run;
         hist[nbins + b] = run + (p & 1023u);
@@ -142,6 +170,7 @@ __global__ __launch_bounds__(BIN_THREADS) void k_bin_fill(Src src,
 
 // Stable LSD radix pass source: 8 bits of 32-bit keys from `shift`, values carried along.
 struct RadixSrc {
+    static constexpr bool RADIX = true;   // one slice of 256 keys
     const uint32_t *keys_in, *vals_in;
     uint32_t *keys_out, *vals_out;
     int items;
@@ -159,6 +188,7 @@ struct RadixSrc {
         return it;
     }
     __device__ void prepare(int, int, Item &) const {}
+    __device__ void begin_fill() const {}
     __device__ void emit(int, int item, const Item &, int, unsigned, uint32_t pos) const
     {
         if (pos < (uint32_t)items) {
@@ -167,6 +197,8 @@ struct RadixSrc {
         }
     }
 };
+
+#define BIN_SELF_BLOCKS 96
 
 // Count, scan and place (see above); the scan runs over (slice, key, block) counts, which cnt
 // holds followed by the waves' offsets (2 cnt_elems words).
@@ -183,30 +215,38 @@ static inline hipError_t launch_binning(const Src &src, int slices, int nbins, i
     uint32_t *pre = cnt + cnt_elems;
     const size_t lds = (size_t)BIN_WAVES * nbins * sizeof(uint32_t);
     const bool small = items == DIGS_BIN_ITEMS_SMALL;
+    // A radix pass over few blocks sums the counts where it needs them: two launches less, 9 us a
+    // pass, for at most BIN_SELF_BLOCKS rows of 1 KiB read by each workgroup (50 blocks: k_bin_fill 8
+    // -> 10 us). With the keys formed in the first pass, the cell sort of 50k Gaussians takes 36 us
+    // in 5 launches instead of 66 in 11.
+    const bool self = Src::RADIX && !small && nblk <= BIN_SELF_BLOCKS;
+    auto count = k_bin_count<Src, DIGS_BIN_ITEMS, false>;
+    auto fill = k_bin_fill<Src, DIGS_BIN_ITEMS, false>;
+    if constexpr (Src::RADIX) {
+        if (self) {
+            count = k_bin_count<Src, DIGS_BIN_ITEMS, true>;
+            fill = k_bin_fill<Src, DIGS_BIN_ITEMS, true>;
+        }
+    } else if (small) {
+        count = k_bin_count<Src, DIGS_BIN_ITEMS_SMALL, false>;
+        fill = k_bin_fill<Src, DIGS_BIN_ITEMS_SMALL, false>;
+    }
     {
         ProfScope ps(stages ? PS_BIN_COUNT : -1, s);
-        if (small)
-            hipLaunchKernelGGL((k_bin_count<Src, DIGS_BIN_ITEMS_SMALL>), dim3(nblk, slices),
-                               dim3(BIN_THREADS), lds, s, src, cnt, pre, nbins, nblk);
-        else
-            hipLaunchKernelGGL((k_bin_count<Src, DIGS_BIN_ITEMS>), dim3(nblk, slices),
-                               dim3(BIN_THREADS), lds, s, src, cnt, pre, nbins, nblk);
+        hipLaunchKernelGGL(count, dim3(nblk, slices), dim3(BIN_THREADS), lds, s, src, cnt, pre,
+                           nbins, nblk);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    {
+    if (!self) {
         ProfScope ps(stages ? PS_SCAN : -1, s);
         e = launch_exclusive_scan(cnt, cnt_elems, scratch, s);
     }
     if (e != hipSuccess) return e;
     {
         ProfScope ps(stages ? PS_BIN_FILL : -1, s);
-        if (small)
-            hipLaunchKernelGGL((k_bin_fill<Src, DIGS_BIN_ITEMS_SMALL>), dim3(nblk, slices),
-                               dim3(BIN_THREADS), lds, s, src, cnt, pre, nbins, nblk, nbits);
-        else
-            hipLaunchKernelGGL((k_bin_fill<Src, DIGS_BIN_ITEMS>), dim3(nblk, slices),
-                               dim3(BIN_THREADS), lds, s, src, cnt, pre, nbins, nblk, nbits);
+        hipLaunchKernelGGL(fill, dim3(nblk, slices), dim3(BIN_THREADS), lds, s, src, cnt, pre,
+                           nbins, nblk, nbits);
     }
     return hipGetLastError();
 }

@@ -45,7 +45,8 @@
 
 // ------------------------------------------------------------------------------------------
 // Diagnostics and small fills
-__global__ void k_diag_begin(DiagBlock *d, unsigned long long cap, uint32_t *cnt_last)
+__device__ __forceinline__ void diag_begin(DiagBlock *d, unsigned long long cap,
+                                           uint32_t *cnt_last)
 {
     if (d->stamp != DIAG_STAMP) diag_clear(d);
     d->instances = 0;
@@ -53,10 +54,9 @@ __global__ void k_diag_begin(DiagBlock *d, unsigned long long cap, uint32_t *cnt
     *cnt_last = 0;
 }
 
-__global__ void k_diag_check(DiagBlock *d)
+__global__ void k_diag_begin(DiagBlock *d, unsigned long long cap, uint32_t *cnt_last)
 {
-    if (d->instances > d->capacity) d->overflow = 1u;
-    if (d->instances > d->max_instances) d->max_instances = d->instances;
+    diag_begin(d, cap, cnt_last);
 }
 
 __global__ void k_fill_f32(float *p, size_t count, float v)
@@ -107,8 +107,10 @@ __global__ __launch_bounds__(256) void k_ffd_canonical(DevGrid g, const float *_
                                                        const float *__restrict__ rho,
                                                        const uint32_t *__restrict__ order,
                                                        float *__restrict__ uv,
-                                                       float *__restrict__ gs)
+                                                       float *__restrict__ gs, DiagBlock *diag,
+                                                       unsigned long long cap, uint32_t *cnt_last)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) diag_begin(diag, cap, cnt_last);
     // four lanes per Gaussian: lane `part` takes the stencil's z index part, and the four partial
     // sums are added in a fixed order. The control points the workgroup's 64 Gaussians reach
     // (neighbours in cell order) are staged in LDS first.
@@ -591,6 +593,8 @@ __device__ __forceinline__ uint32_t block_mask(const FootEll &fe, int tx, int ty
 
 template <int TW, int TH>   // tile shape (pixels)
 struct TileSrc {
+    static constexpr bool RADIX = false;
+    DiagBlock *diag;
     const int4 *rect;        // [T][N] footprint rectangles and instance masks (TileRect)
     const float4 *rec;       // [T][N][4] projected records (footprint conic in rec[2].w, rec[3])
     uint32_t *list;
@@ -644,6 +648,12 @@ struct TileSrc {
         it.fe.cx = it.fe.cy = it.fe.s = it.fe.ia = it.fe.D = it.fe.ry = it.fe.ryl = 0.0f;
         it.fe.ell = false;
         return it;
+    }
+    // the call's instances, which the set-up has counted, against the capacity
+    __device__ void begin_fill() const
+    {
+        if (diag->instances > diag->capacity) diag->overflow = 1u;
+        if (diag->instances > diag->max_instances) diag->max_instances = diag->instances;
     }
     __device__ void prepare(int t, int item, Item &it) const
     {
@@ -725,6 +735,7 @@ __device__ __forceinline__ void slice_range(uint32_t &begin, uint32_t &end, int 
 #define FWD_HALVES 512              // Gaussians that meet one half, kept to the list's end
 #define FWD_LDS (2 * FWD_QUEUE + FWD_HALVES)
 #define FWD_COLS 40
+#define FWD_SHORT 400u              // lists too short for the lanes (splat_fwd_tile)
 
 // +1 or -1 with the sign of v
 __device__ __forceinline__ float sign_of(float v)
@@ -1183,12 +1194,20 @@ __device__ __forceinline__ void splat_fwd_tile(const DevGeom &G, int n, int t, i
             // A block of whose first 64 entries more than 8 are marked direct goes by columns
             // throughout: setting them aside costs more than the lanes gain (58k Gaussians, 20
             // views of 86x55 pixels of 4.5 mm, nearly all direct: 144 us by this rule, 185 without
-            // it; 200k on 1 mm pixels, nearly none: 4.72 ms by columns, 3.70 by this rule)
+            // it; 200k on 1 mm pixels, nearly none: 4.72 ms by columns, 3.70 by this rule). So does
+            // a list of fewer than FWD_SHORT entries, about two groups of 64 a block, without a look
+            // at its records: there the lanes' sums and remainder cost what they gain (one 256x256
+            // view of 50k Gaussians, about 290 entries: 48 us by lanes, 45 by columns; 375 entries,
+            // 16 views of 64x64: 35.0 and 34.5; 940, 512x512: 83 by lanes, 96 by columns in quarters)
             uint32_t first = LIST_INDEX_MASK;
-            if (begin < end) first = list[min(begin + lane, end - 1)];
-            const uint32_t g = first & LIST_INDEX_MASK;
-            const float huu = g < (uint32_t)n ? rt[(size_t)g * 4].z : -1.0f;
-            if (8 * __popcll(__ballot(!signbit(huu))) > DIGS_WAVE) {
+            bool cols = end - begin < FWD_SHORT;
+            if (!cols) {
+                first = list[min(begin + lane, end - 1)];
+                const uint32_t g = first & LIST_INDEX_MASK;
+                const float huu = g < (uint32_t)n ? rt[(size_t)g * 4].z : -1.0f;
+                cols = 8 * __popcll(__ballot(!signbit(huu))) > DIGS_WAVE;
+            }
+            if (cols) {
                 // (the empty asm keeps what the columns derive from the lane out of the registers
                 // of the other path, which has none to spare)
                 int l = lane;
@@ -2320,24 +2339,46 @@ __global__ __launch_bounds__(256) void k_gw_final(const float *__restrict__ gwpa
 
 // ------------------------------------------------------------------------------------------
 // a8: cell sort and the control-point gather of dL/dcoef
-__global__ void k_cell_keys(DevGrid g, int n, const float *__restrict__ mu,
-                            uint32_t *__restrict__ keys, uint32_t *__restrict__ vals)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float q[3] = {(mu[i] - g.ox) / g.hx, (mu[n + i] - g.oy) / g.hy,
-                        (mu[2 * n + i] - g.oz) / g.hz};
-    const int dims[3] = {g.nx, g.ny, g.nz};
-    int c[3];
+// The first pass of the cell sort: the low 8 bits of the key of each mean's lattice cell, which is
+// formed here and written with the Gaussian's index.
+struct CellSrc {
+    static constexpr bool RADIX = true;
+    DevGrid g;
+    const float *mu;
+    uint32_t *keys_out, *vals_out;
+    int items;
+    struct Item {
+        uint32_t k;
+        __device__ int nkeys() const { return 1; }
+        __device__ int key(int) const { return (int)(k & 255u); }
+        __device__ void count(uint32_t *h) const { atomicAdd(&h[k & 255u], 1u); }
+    };
+    __device__ Item load(int, int i) const
+    {
+        const float q[3] = {(mu[i] - g.ox) / g.hx, (mu[items + i] - g.oy) / g.hy,
+                            (mu[2 * items + i] - g.oz) / g.hz};
+        const int dims[3] = {g.nx, g.ny, g.nz};
+        int c[3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        float f = floorf(q[a]);
-        f = fminf(fmaxf(f, -2.0f), (float)(dims[a] + 1));   // NaN-safe clamp
-        c[a] = (f == f) ? (int)f + 2 : 0;
+        for (int a = 0; a < 3; ++a) {
+            float f = floorf(q[a]);
+            f = fminf(fmaxf(f, -2.0f), (float)(dims[a] + 1));   // NaN-safe clamp
+            c[a] = (f == f) ? (int)f + 2 : 0;
+        }
+        Item it;
+        it.k = ((uint32_t)c[2] * (g.ny + 4) + c[1]) * (g.nx + 4) + c[0];
+        return it;
     }
-    keys[i] = ((uint32_t)c[2] * (g.ny + 4) + c[1]) * (g.nx + 4) + c[0];
-    vals[i] = (uint32_t)i;
-}
+    __device__ void prepare(int, int, Item &) const {}
+    __device__ void begin_fill() const {}
+    __device__ void emit(int, int item, const Item &it, int, unsigned, uint32_t pos) const
+    {
+        if (pos < (uint32_t)items) {
+            keys_out[pos] = it.k;
+            vals_out[pos] = (uint32_t)item;
+        }
+    }
+};
 
 // cell_start[k] = number of Gaussians whose cell key is below k (for every key 0..ncells), by a
 // binary search of the sorted keys per cell; order[p] = the Gaussian at position p in cell order
@@ -2641,12 +2682,21 @@ static hipError_t cell_sort(const RenderArgs &a, hipStream_t s)
     const int n = a.n;
     uint32_t *ka = WS(a, keys_a, uint32_t *), *va = WS(a, vals_a, uint32_t *);
     uint32_t *kb = WS(a, keys_b, uint32_t *), *vb = WS(a, vals_b, uint32_t *);
-    hipLaunchKernelGGL(k_cell_keys, dim3((n + 255) / 256), dim3(256), 0, s, a.grid, n, a.mu, ka,
-                       va);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     const int nblk_r = (n + DIGS_BIN_ITEMS - 1) / DIGS_BIN_ITEMS;
     const int kbits = bits_for(a.L.ncells);
-    for (int shift = 0; shift < kbits; shift += 8) {
+    uint32_t *rhist = WS(a, rhist, uint32_t *), *scratch = WS(a, scratch, uint32_t *);
+    {
+        CellSrc src;
+        src.g = a.grid;
+        src.mu = a.mu;
+        src.keys_out = ka;
+        src.vals_out = va;
+        src.items = n;
+        e = launch_binning(src, 1, 256, nblk_r, 8, rhist, (size_t)256 * nblk_r, scratch, s,
+                           DIGS_BIN_ITEMS, false);
+        if (e != hipSuccess) return e;
+    }
+    for (int shift = 8; shift < kbits; shift += 8) {
         RadixSrc src;
         src.keys_in = ka;
         src.vals_in = va;
@@ -2654,9 +2704,8 @@ static hipError_t cell_sort(const RenderArgs &a, hipStream_t s)
         src.vals_out = vb;
         src.items = n;
         src.shift = shift;
-        e = launch_binning(src, 1, 256, nblk_r, 8, WS(a, rhist, uint32_t *),
-                           (size_t)256 * nblk_r, WS(a, scratch, uint32_t *), s, DIGS_BIN_ITEMS,
-                           false);
+        e = launch_binning(src, 1, 256, nblk_r, 8, rhist, (size_t)256 * nblk_r, scratch, s,
+                           DIGS_BIN_ITEMS, false);
         if (e != hipSuccess) return e;
         uint32_t *t0 = ka; ka = kb; kb = t0;
         t0 = va; va = vb; vb = t0;
@@ -2666,6 +2715,12 @@ static hipError_t cell_sort(const RenderArgs &a, hipStream_t s)
                        a.L.ncells,
                        ka, va, WS(a, cell_start, uint32_t *), WS(a, order, uint32_t *));
     return hipGetLastError();
+}
+
+// The last of the tile lists' counts, one past every list: zero, so that its scan is the total
+static uint32_t *count_end(const RenderArgs &a)
+{
+    return WS(a, cnt, uint32_t *) + (size_t)a.T * a.geom.ntiles * a.L.nblk;
 }
 
 // The per-Gaussian stage (cell order, the Gaussians gathered into it, the FFD at the canonical
@@ -2681,7 +2736,8 @@ hipError_t render_forward_canonical(const RenderArgs &a, hipStream_t s)
         hipLaunchKernelGGL(kernel, dim3((unsigned)(((size_t)4 * a.n + 255) / 256)),
                            dim3(256), 0, s, a.grid,
                            a.coef, a.basis, a.n, a.mu, a.scale, a.quat, a.rho,
-                           WS(a, order, const uint32_t *), WS(a, uv, float *), WS(a, gsort, float *));
+                           WS(a, order, const uint32_t *), WS(a, uv, float *), WS(a, gsort, float *),
+                           WS(a, diag, DiagBlock *), (unsigned long long)a.L.cap, count_end(a));
     }
     return hipGetLastError();
 }
@@ -2690,7 +2746,7 @@ hipError_t render_forward_setup(const RenderArgs &a, hipStream_t s)
 {
     hipError_t e = render_forward_canonical(a, s);
     if (e != hipSuccess) return e;
-    return render_forward_views(a, s);
+    return render_forward_views(a, s, false);
 }
 
 // The tile lists of the call's (view, Gaussian) instances, binned for a TW x TH tile shape.
@@ -2699,6 +2755,7 @@ static hipError_t bin_tiles(const RenderArgs &a, uint32_t *cnt, size_t cnt_elems
                             uint32_t *scratch, hipStream_t s)
 {
     TileSrc<TW, TH> src;
+    src.diag = WS(a, diag, DiagBlock *);
     src.rect = WS(a, rect, const int4 *);
     src.rec = WS(a, rec, const float4 *);
     src.list = WS(a, list, uint32_t *);
@@ -2711,14 +2768,17 @@ static hipError_t bin_tiles(const RenderArgs &a, uint32_t *cnt, size_t cnt_elems
 }
 
 // The per-view stages: the warp and projected records, instance offsets and the tile lists.
-hipError_t render_forward_views(const RenderArgs &a, hipStream_t s)
+// begin: without the per-Gaussian stage before it, which otherwise begins the diagnostics.
+hipError_t render_forward_views(const RenderArgs &a, hipStream_t s, bool begin)
 {
     hipError_t e;
     const size_t cnt_elems = (size_t)a.T * a.geom.ntiles * a.L.nblk;
     uint32_t *cnt = WS(a, cnt, uint32_t *);
-    hipLaunchKernelGGL(k_diag_begin, dim3(1), dim3(1), 0, s, WS(a, diag, DiagBlock *),
-                       (unsigned long long)a.L.cap, cnt + cnt_elems);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (begin) {
+        hipLaunchKernelGGL(k_diag_begin, dim3(1), dim3(1), 0, s, WS(a, diag, DiagBlock *),
+                           (unsigned long long)a.L.cap, count_end(a));
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     {
         ProfScope ps(PS_SETUP, s);
         switch (a.grid.R) {
@@ -2743,9 +2803,7 @@ hipError_t render_forward_views(const RenderArgs &a, hipStream_t s)
     else if (th == 32) e = bin_tiles<8, 32>(a, cnt, cnt_elems, scratch, s);
     else if (th == 16) e = bin_tiles<8, 16>(a, cnt, cnt_elems, scratch, s);
     else e = bin_tiles<8, 8>(a, cnt, cnt_elems, scratch, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_diag_check, dim3(1), dim3(1), 0, s, WS(a, diag, DiagBlock *));
-    return hipGetLastError();
+    return e;
 }
 
 // Workgroups of a persistent launch: enough to fill every CU at the kernel's occupancy, never more
