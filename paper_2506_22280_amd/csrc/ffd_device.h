@@ -139,40 +139,49 @@ __device__ __forceinline__ void ffd_rank(const DevGrid &g, const float *__restri
     ffd_rank_rows<NZ>(LatticeRows{coef, g.nx, g.ny, g.nz}, r, s, u, J, nz0);
 }
 
-// sum_{a,b} Q[3a+b] * d^2 u_a / dx_b dx_c for one rank (the term of dL/dmu through K(mu)),
-// accumulated into h[c] (over the stencil's z indices n0..n1-1). The z and y loops stay rolled
-// (registers); their per-index values are selected.
-template <class Rows>
-__device__ __forceinline__ void ffd_rank_hessian_contract(const Rows &rows, int r,
-                                                          const Stencil &s, const float Q[9],
-                                                          float h[3], int n0 = 0, int n1 = 4)
+// sum_r sum_{a,b} Q[r][3a+b] * d^2 u_{r,a} / dx_b dx_c (the term of dL/dmu through K(mu)) over the
+// stencil's z index n, accumulated into h[c]. The ranks are contracted first, control point by
+// control point: the six weights of the second derivatives are formed once for all of them, and a
+// lattice row's loads (4 points of every rank) are in flight together. The y loop stays rolled
+// (registers); its values are selected.
+template <int NR>
+__device__ __forceinline__ void ffd_hessian_contract(const DevGrid &g,
+                                                     const float *__restrict__ coef,
+                                                     const Stencil &s, const float (&Q)[NR][9],
+                                                     float h[3], int n)
 {
+    const LatticeRows rows{coef, g.nx, g.ny, g.nz};
+    const int kk = pick4(s.kk, n);
+    const float Bz = pick4(s.Bz, n), dBz = pick4(s.dBz, n), d2Bz = pick4(s.d2Bz, n);
 #pragma unroll 1
-    for (int n = n0; n < n1; ++n) {
-        const int kk = pick4(s.kk, n);
-        const float Bz = pick4(s.Bz, n), dBz = pick4(s.dBz, n), d2Bz = pick4(s.d2Bz, n);
-#pragma unroll 1
-        for (int m = 0; m < 4; ++m) {
-            const int jj = pick4(s.jj, m);
-            const float By = pick4(s.By, m), dBy = pick4(s.dBy, m), d2By = pick4(s.d2By, m);
+    for (int m = 0; m < 4; ++m) {
+        const int jj = pick4(s.jj, m);
+        const float By = pick4(s.By, m), dBy = pick4(s.dBy, m), d2By = pick4(s.d2By, m);
+        // y_b = sum_r sum_a Q_r[a][b] d_{r,a}
+        float y[4][3];
+#pragma unroll
+        for (int l = 0; l < 4; ++l) y[l][0] = y[l][1] = y[l][2] = 0.0f;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
             const float *row = rows.row(r, kk, jj);
 #pragma unroll
             for (int l = 0; l < 4; ++l) {
                 const float *d = row + s.ii[l] * 3;
-                // y_b = sum_a Q[a][b] d_a
-                float y[3];
 #pragma unroll
-                for (int b = 0; b < 3; ++b) y[b] = Q[b] * d[0] + Q[3 + b] * d[1] + Q[6 + b] * d[2];
-                const float wxx = s.d2Bx[l] * By * Bz;
-                const float wyy = s.Bx[l] * d2By * Bz;
-                const float wzz = s.Bx[l] * By * d2Bz;
-                const float wxy = s.dBx[l] * dBy * Bz;
-                const float wxz = s.dBx[l] * By * dBz;
-                const float wyz = s.Bx[l] * dBy * dBz;
-                h[0] += wxx * y[0] + wxy * y[1] + wxz * y[2];
-                h[1] += wxy * y[0] + wyy * y[1] + wyz * y[2];
-                h[2] += wxz * y[0] + wyz * y[1] + wzz * y[2];
+                for (int b = 0; b < 3; ++b)
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) y[l][b] = fmaf(Q[r][3 * a + b], d[a], y[l][b]);
             }
+        }
+        const float yz = By * Bz, yyz = d2By * Bz, yzz = By * d2Bz, dyz = dBy * Bz, ydz = By * dBz,
+                    dydz = dBy * dBz;
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            const float wxx = s.d2Bx[l] * yz, wyy = s.Bx[l] * yyz, wzz = s.Bx[l] * yzz,
+                        wxy = s.dBx[l] * dyz, wxz = s.dBx[l] * ydz, wyz = s.Bx[l] * dydz;
+            h[0] += wxx * y[l][0] + wxy * y[l][1] + wxz * y[l][2];
+            h[1] += wxy * y[l][0] + wyy * y[l][1] + wyz * y[l][2];
+            h[2] += wxz * y[l][0] + wyz * y[l][1] + wzz * y[l][2];
         }
     }
 }

@@ -2155,50 +2155,66 @@ __global__ __launch_bounds__(256, NR <= 3 ? 3 : 1) void k_tn_bwd(
     }
 }
 
+// v of lane l of the quad
+__device__ __forceinline__ float quad_lane(float v, int l)
+{
+    const int x = __float_as_int(v);
+    return __int_as_float(l == 0   ? __builtin_amdgcn_mov_dpp(x, 0x00, 0xf, 0xf, true)
+                          : l == 1 ? __builtin_amdgcn_mov_dpp(x, 0x55, 0xf, 0xf, true)
+                          : l == 2 ? __builtin_amdgcn_mov_dpp(x, 0xaa, 0xf, 0xf, true)
+                                   : __builtin_amdgcn_mov_dpp(x, 0xff, 0xf, 0xf, true));
+}
+
 // added to the cell's x index in the sources of dL/dcoef of a Gaussian with a non-finite P or Q
 #define CG_BAD (1 << 20)
 
+// Four lanes per Gaussian: lane `part` adds a quarter of the chunks' fields and of V^T P, takes the
+// stencil's z index part in the second-derivative term (partial sums added in a fixed order) and
+// writes a quarter of the row for k_coef_grad; lane 0 writes the results. (The lattice is read
+// through the caches: staging the workgroup's control points in LDS, as the canonical FFD does,
+// made this kernel slower.) Bound by the latency of its loads with few Gaussians and by their
+// number with many: registers for loads in flight are worth more than wavefronts, hence the cap on
+// those. With every lane adding every field and lane 0 writing the row, one rank's second
+// derivatives after the other's, it took 30 us for 4k Gaussians and 16 views (now 18), 143 for 200k
+// and 64 (107), 377 for 500k, R = 4 (288; 350 without the cap), 31 for 80k, R = 2 (28).
 template <int NR>
-__global__ __launch_bounds__(256) void k_gauss_reduce(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, NR <= 3 ? 3 : 2)))
+void k_gauss_reduce(
     DevGrid grid, int n, int nch, const float *__restrict__ coef, const float *__restrict__ gpar,
     const float *__restrict__ uv, const float *__restrict__ tacc,
     const uint32_t *__restrict__ order, float *__restrict__ g_mu, float *__restrict__ g_scale,
     float *__restrict__ g_quat, float *__restrict__ g_rho, float *__restrict__ gq, int gq_stride,
     float *__restrict__ g_basis)
 {
-    // four lanes per Gaussian: lane `part` takes the stencil's z index part in the second-
-    // derivative term (partial sums added in a fixed order); lane 0 writes the results. (The
-    // lattice is read through the caches here: staging the workgroup's control points in LDS, as
-    // the canonical FFD does, made this kernel slower.)
     const int gt = blockIdx.x * blockDim.x + threadIdx.x;
     const int i = gt >> 2, part = gt & 3;
     if (i >= n) return;
-    float gsum[3] = {0.f, 0.f, 0.f}, gRS[9], P[NR][3], Q[NR][9], grho = 0.0f;
+    // the chunks of views, in order: lane `part` adds fields part, part + 4, ..., and the quad's lanes
+    // then hand each other the sums
+    constexpr int NF = 13 + 12 * NR, NK = (NF + 3) / 4;
+    float f[NK];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) gRS[k] = 0.0f;
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) P[r][a] = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) Q[r][k] = 0.0f;
-    }
-    // the chunks of views, in order
+    for (int k = 0; k < NK; ++k) f[k] = 0.0f;
     const size_t fs = (size_t)nch * n;
     for (int c = 0; c < nch; ++c) {
         const float *src = tacc + (size_t)c * n + i;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) gsum[a] += src[a * fs];
+        for (int k = 0; k < NK; ++k) f[k] += src[(size_t)min(4 * k + part, NF - 1) * fs];
+    }
+    float gsum[3], gRS[9], P[NR][3], Q[NR][9];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) gRS[k] += src[(3 + k) * fs];
-        grho += src[12 * fs];
+    for (int a = 0; a < 3; ++a) gsum[a] = quad_lane(f[a >> 2], a & 3);
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
+    for (int k = 0; k < 9; ++k) gRS[k] = quad_lane(f[(3 + k) >> 2], (3 + k) & 3);
+    float grho = quad_lane(f[3], 0);
 #pragma unroll
-            for (int a = 0; a < 3; ++a) P[r][a] += src[(13 + 12 * r + a) * fs];
+    for (int r = 0; r < NR; ++r) {
 #pragma unroll
-            for (int k = 0; k < 9; ++k) Q[r][k] += src[(16 + 12 * r + k) * fs];
-        }
+        for (int a = 0; a < 3; ++a)
+            P[r][a] = quad_lane(f[(13 + 12 * r + a) >> 2], (13 + 12 * r + a) & 3);
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+            Q[r][k] = quad_lane(f[(16 + 12 * r + k) >> 2], (16 + 12 * r + k) & 3);
     }
     // dL/dmu = sum_t dL/dmu' + sum_r V_r^T P_r + sum_r Q_r : d(grad u_r)/dmu (with a per-Gaussian
     // basis, u and V do not depend on mu: the first term only)
@@ -2206,20 +2222,23 @@ __global__ __launch_bounds__(256) void k_gauss_reduce(
     const size_t src = order[i];   // i is the position in cell order
     Stencil st;
     if (!g_basis) {
-#pragma unroll
-        for (int r = 0; r < NR; ++r)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const float *V = uv + ((size_t)3 * NR + r * 9) * n + i;
-                gmu[c] += V[c * (size_t)n] * P[r][0] + V[(3 + c) * (size_t)n] * P[r][1] +
-                          V[(6 + c) * (size_t)n] * P[r][2];
-            }
-        const float mu0[3] = {gpar[i], gpar[(size_t)n + i], gpar[(size_t)2 * n + i]};
-        make_stencil(grid, mu0[0], mu0[1], mu0[2], st, true);
-        const LatticeRows lr{coef, grid.nx, grid.ny, grid.nz};
+        // (rank, component) pair 3 r + a of V^T P is lane (3 r + a) % 4's
         float hs[3] = {0.f, 0.f, 0.f};
 #pragma unroll
-        for (int r = 0; r < NR; ++r) ffd_rank_hessian_contract(lr, r, st, Q[r], hs, part, part + 1);
+        for (int k = 0; k < (3 * NR + 3) / 4; ++k) {
+            const int q = 4 * k + part;
+            float pq = 0.0f;
+#pragma unroll
+            for (int l = 0; l < 4; ++l)
+                if (4 * k + l < 3 * NR) pq = part == l ? P[(4 * k + l) / 3][(4 * k + l) % 3] : pq;
+            const float *V = uv + ((size_t)3 * NR + 3 * min(q, 3 * NR - 1)) * n + i;
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                hs[c] = fmaf(V[c * (size_t)n], pq, hs[c]);
+        }
+        const float mu0[3] = {gpar[i], gpar[(size_t)n + i], gpar[(size_t)2 * n + i]};
+        make_stencil(grid, mu0[0], mu0[1], mu0[2], st, true);
+        ffd_hessian_contract<NR>(grid, coef, st, Q, hs, part);
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             hs[a] += __shfl_xor(hs[a], 1, DIGS_WAVE);
@@ -2268,21 +2287,19 @@ __global__ __launch_bounds__(256) void k_gauss_reduce(
     float gqh[4];
     quat_rot_adjoint(qh[0], qh[1], qh[2], qh[3], gR, gqh);
     const float dq = gqh[0] * qh[0] + gqh[1] * qh[1] + gqh[2] * qh[2] + gqh[3] * qh[3];
-    if (part != 0) return;
+    if (part == 0) {
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        g_mu[(size_t)a * n + src] = gmu[a];
-        g_scale[(size_t)a * n + src] = gs[a];
+        for (int a = 0; a < 3; ++a) {
+            g_mu[(size_t)a * n + src] = gmu[a];
+            g_scale[(size_t)a * n + src] = inputs_ok ? gs[a] : 0.0f;
+        }
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+            g_quat[(size_t)a * n + src] = inputs_ok ? (gqh[a] - dq * qh[a]) * qn : 0.0f;
+        g_rho[src] = grho;
     }
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-        g_quat[(size_t)a * n + src] = inputs_ok ? (gqh[a] - dq * qh[a]) * qn : 0.0f;
-    if (!inputs_ok) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) g_scale[(size_t)a * n + src] = 0.0f;
-    }
-    g_rho[src] = grho;
     if (g_basis) {   // dL/du_r = P_r, dL/dV_r = Q_r, at the Gaussian's own index
+        if (part != 0) return;
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             float *b = g_basis + (size_t)r * 12 * n + src;
@@ -2293,30 +2310,40 @@ __global__ __launch_bounds__(256) void k_gauss_reduce(
         }
         return;
     }
-    // sources of dL/dcoef in cell order: clamped cell, fraction, P_r, Q_r
-    float *o = gq + (size_t)i * gq_stride;
+    // sources of dL/dcoef in cell order: clamped cell, fraction, [P, Q_x, Q_y, Q_z][rank][component];
+    // the quad writes the row (an even number of floats) two at a time, side by side
     bool finite = true;   // (k_coef_grad keeps a NaN or an infinity to the points it belongs to)
+    float o[6 + 12 * NR];
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
+    for (int r = 0; r < NR; ++r)
 #pragma unroll
-        for (int a = 0; a < 3; ++a) finite = finite && isfinite(P[r][a]);
+        for (int a = 0; a < 3; ++a) {
+            o[6 + 3 * r + a] = P[r][a];
+            finite = finite && isfinite(P[r][a]);
 #pragma unroll
-        for (int k = 0; k < 9; ++k) finite = finite && isfinite(Q[r][k]);
-    }
+            for (int c = 0; c < 3; ++c) {
+                o[6 + 3 * NR * (c + 1) + 3 * r + a] = Q[r][3 * a + c];
+                finite = finite && isfinite(Q[r][3 * a + c]);
+            }
+        }
     o[0] = __int_as_float(max(-2, min(st.fx, grid.nx + 1)) + (finite ? 0 : CG_BAD));
     o[1] = __int_as_float(max(-2, min(st.fy, grid.ny + 1)));
     o[2] = __int_as_float(max(-2, min(st.fz, grid.nz + 1)));
     o[3] = inputs_ok ? st.px : 0.0f;
     o[4] = inputs_ok ? st.py : 0.0f;
     o[5] = inputs_ok ? st.pz : 0.0f;
+    float2 *row = (float2 *)(gq + (size_t)i * gq_stride);
+    constexpr int NP = 3 + 6 * NR;
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
+    for (int k = 0; k < (NP + 3) / 4; ++k) {
+        float2 v = make_float2(0.0f, 0.0f);
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {   // [P, Q_x, Q_y, Q_z][rank][component]
-            o[6 + 3 * r + a] = P[r][a];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) o[6 + 3 * NR * (c + 1) + 3 * r + a] = Q[r][3 * a + c];
-        }
+        for (int l = 0; l < 4; ++l)
+            if (4 * k + l < NP) {
+                v.x = part == l ? o[2 * (4 * k + l)] : v.x;
+                v.y = part == l ? o[2 * (4 * k + l) + 1] : v.y;
+            }
+        if (4 * k + part < NP) row[4 * k + part] = v;
     }
 }
 
