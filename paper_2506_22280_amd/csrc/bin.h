@@ -57,10 +57,10 @@ __global__ __launch_bounds__(BIN_THREADS) void k_bin_count(Src src, uint32_t *__
     __syncthreads();
     uint32_t *h = hist + wave * nbins;
     constexpr int PER_WAVE = ITEMS / BIN_WAVES;
-    const int base = blk * ITEMS + wave * PER_WAVE;
+    const int base = blk * ITEMS + wave * PER_WAVE, nitems = src.count();
     for (int step = 0; step < PER_WAVE / DIGS_WAVE; ++step) {
         const int item = base + step * DIGS_WAVE + lane;
-        if (item < src.items) src.load(slice, item).count(h);
+        if (item < nitems) src.load(slice, item).count(h);
     }
     __syncthreads();
     for (int b = threadIdx.x; b < nbins; b += BIN_THREADS) {
@@ -89,6 +89,8 @@ __global__ __launch_bounds__(BIN_THREADS) void k_bin_fill(Src src,
     constexpr int PER_WAVE = ITEMS / BIN_WAVES;
     const int base = blk * ITEMS + wave * PER_WAVE;
     if (slice == 0 && blk == 0 && threadIdx.x == 0) src.begin_fill();
+    const int nitems = src.count();
+    if (blk * ITEMS >= nitems) return;   // (the whole workgroup)
     uint32_t self = 0;
     if constexpr (SELF) {
         __shared__ uint32_t wave_total[BIN_WAVES];
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(BIN_THREADS) void k_bin_fill(Src src,
     for (int step = 0; step < PER_WAVE / DIGS_WAVE; ++step) {
         const int item0 = base + step * DIGS_WAVE;
         const int item = item0 + lane;
-        const bool valid = item < src.items;
+        const bool valid = item < nitems;
         typename Src::Item it = src.load(slice, valid ? item : 0);
         if (valid) src.prepare(slice, item, it);
         const int nk = valid ? it.nkeys() : 0;
@@ -175,6 +177,8 @@ struct RadixSrc {
     uint32_t *keys_out, *vals_out;
     int items;
     int shift;
+    const uint32_t *total;   // if not null, the number of items is *total, at most `items`
+    __device__ int count() const { return total ? (int)min(*total, (uint32_t)items) : items; }
     struct Item {
         uint32_t k;
         __device__ int nkeys() const { return 1; }
@@ -261,10 +265,13 @@ static inline int bits_for(int nbins)
 
 // Stable sort of (key, value) pairs by the low `kbits` bits of the key, 8 bits per pass. The
 // pairs start in (ka, va); the sorted pairs end in (ka, va) if *swapped is false, else in
-// (kb, vb). rhist needs 2 * 256 * ceil(n / DIGS_BIN_ITEMS) words, scratch the scan's scratch.
+// (kb, vb). rhist needs 2 * 256 * ceil(n / DIGS_BIN_ITEMS) words, scratch the scan's scratch. With
+// total (a device word) only the first *total pairs, at most n, are there and are sorted: the
+// workgroups past them count nothing and return.
 static inline hipError_t radix_sort_pairs(uint32_t *ka, uint32_t *va, uint32_t *kb, uint32_t *vb,
                                           int n, int kbits, uint32_t *rhist, uint32_t *scratch,
-                                          bool *swapped, hipStream_t s)
+                                          bool *swapped, hipStream_t s,
+                                          const uint32_t *total = nullptr)
 {
     *swapped = false;
     const int nblk = (n + DIGS_BIN_ITEMS - 1) / DIGS_BIN_ITEMS;
@@ -276,6 +283,7 @@ static inline hipError_t radix_sort_pairs(uint32_t *ka, uint32_t *va, uint32_t *
         src.vals_out = *swapped ? va : vb;
         src.items = n;
         src.shift = shift;
+        src.total = total;
         hipError_t e = launch_binning(src, 1, 256, nblk, 8, rhist, (size_t)256 * nblk, scratch, s);
         if (e != hipSuccess) return e;
         *swapped = !*swapped;

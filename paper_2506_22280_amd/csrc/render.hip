@@ -602,6 +602,7 @@ struct TileSrc {
     int items;               // N
     int tiles_x;
     float inv_tiles_x;       // 1 / tiles_x
+    __device__ int count() const { return items; }
     struct Item {
         TileRect tr;
         int cnt, tiles_x;
@@ -2374,6 +2375,7 @@ struct CellSrc {
     const float *mu;
     uint32_t *keys_out, *vals_out;
     int items;
+    __device__ int count() const { return items; }
     struct Item {
         uint32_t k;
         __device__ int nkeys() const { return 1; }
@@ -2731,6 +2733,7 @@ static hipError_t cell_sort(const RenderArgs &a, hipStream_t s)
         src.vals_out = vb;
         src.items = n;
         src.shift = shift;
+        src.total = nullptr;
         e = launch_binning(src, 1, 256, nblk_r, 8, rhist, (size_t)256 * nblk_r, scratch, s,
                            DIGS_BIN_ITEMS, false);
         if (e != hipSuccess) return e;

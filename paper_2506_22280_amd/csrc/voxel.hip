@@ -558,24 +558,12 @@ __global__ __launch_bounds__(256) void k_phi_emit(int n, const int2 *__restrict_
             }
 }
 
-// Pairs past the emitted ones (from *total to cap) get a key past every brick, so that they sort
-// last and no brick's range reaches them.
-__global__ __launch_bounds__(256) void k_phi_tail_keys(const uint32_t *__restrict__ total,
-                                                       size_t cap, uint32_t sentinel,
-                                                       uint32_t *__restrict__ keys,
-                                                       uint32_t *__restrict__ vals)
+// bstart[b] = position of the first pair of brick b in sorted order (for every b in 0..nbricks) of the
+// m = min(*total, cap) pairs
+__global__ void k_brick_start(const uint32_t *__restrict__ total, int cap, int nbricks,
+                              const uint32_t *__restrict__ keys, uint32_t *__restrict__ bstart)
 {
-    const size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= cap || p < (size_t)*total) return;
-    keys[p] = sentinel;
-    vals[p] = 0u;
-}
-
-// bstart[b] = position of the first pair of brick b in sorted order (for every b in 0..nbricks)
-__global__ void k_brick_start(int m, int nbricks, const uint32_t *__restrict__ keys,
-                              uint32_t *__restrict__ bstart)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = blockIdx.x * blockDim.x + threadIdx.x, m = (int)min(*total, (uint32_t)cap);
     if (p > m) return;
     const uint32_t hi = (p < m) ? min(keys[p], (uint32_t)nbricks) : (uint32_t)nbricks;
     const uint32_t lo = (p > 0) ? min(keys[p - 1], (uint32_t)nbricks) + 1u : 0u;
@@ -753,18 +741,15 @@ extern "C" int digs_phi_grid(const digs_grid *grid, const float *coef, int n, co
     hipLaunchKernelGGL(k_phi_emit, dim3((n + 255) / 256), dim3(256), 0, s, n,
                        (const int2 *)(W + L.brange), count, L.nbx, L.nby, L.cap, ka, va, diag);
     if ((e = hipGetLastError()) != hipSuccess) return digs_set_hip_error(e);
-    // The pair count is known only on the device; the sort and the splat run over the capacity
-    // and clamp to it (pairs past the emitted ones carry keys past every brick).
-    hipLaunchKernelGGL(k_phi_tail_keys, dim3((unsigned)((L.cap + 255) / 256)), dim3(256), 0, s,
-                       count + n, L.cap, (uint32_t)L.nbricks, ka, va);
-    if ((e = hipGetLastError()) != hipSuccess) return digs_set_hip_error(e);
+    // The pair count is known only on the device: the sort and the starts are launched over the
+    // capacity, and what lies past the pairs returns at once.
     bool swapped = false;
-    e = radix_sort_pairs(ka, va, kb, vb, (int)L.cap, bits_for(L.nbricks + 1),
-                         (uint32_t *)(W + L.rhist), scratch, &swapped, s);
+    e = radix_sort_pairs(ka, va, kb, vb, (int)L.cap, bits_for(L.nbricks),
+                         (uint32_t *)(W + L.rhist), scratch, &swapped, s, count + n);
     if (e != hipSuccess) return digs_set_hip_error(e);
     const uint32_t *keys = swapped ? kb : ka, *vals = swapped ? vb : va;
     hipLaunchKernelGGL(k_brick_start, dim3((unsigned)((L.cap + 1 + 255) / 256)), dim3(256), 0, s,
-                       (int)L.cap, L.nbricks, keys, (uint32_t *)(W + L.bstart));
+                       count + n, (int)L.cap, L.nbricks, keys, (uint32_t *)(W + L.bstart));
     if ((e = hipGetLastError()) != hipSuccess) return digs_set_hip_error(e);
     hipLaunchKernelGGL(k_phi_splat, dim3(L.nbricks), dim3(256), 0, s, v, L.nbx, L.nby,
                        (const float *)(W + L.rec), vals, (const uint32_t *)(W + L.bstart), L.cap,
