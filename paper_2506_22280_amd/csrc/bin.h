@@ -134,6 +134,20 @@ __global__ __launch_bounds__(BIN_THREADS) void k_bin_fill(Src src,
         const bool valid = item < nitems;
         typename Src::Item it = src.load(slice, valid ? item : 0);
         if (valid) src.prepare(slice, item, it);
+        // places one (item, key) pair per active lane
+        const auto place = [&](bool active, int index, const typename Src::Item &o, int k,
+                               unsigned key) {
+            const unsigned long long peers = wave_match(key, active, nbits);
+            uint32_t pos = 0;
+            const int rank = lane_rank(peers);
+            if (active) pos = h[key] + (uint32_t)rank;
+            if (active && rank == 0) h[key] = pos + (uint32_t)__popcll(peers);
+            if (active) src.emit(slice, index, o, k, key, pos);
+        };
+        if constexpr (Src::RADIX) {   // one key an item: the lane's own, nothing to flatten
+            place(valid, item, it, 0, valid ? (unsigned)it.key(0) : 0u);
+            continue;
+        }
         const int nk = valid ? it.nkeys() : 0;
         int incl = nk;
 #pragma unroll
@@ -157,13 +171,7 @@ __global__ __launch_bounds__(BIN_THREADS) void k_bin_fill(Src src,
                 if (starts[wave][j + b] <= idx) j += b;
             const int k = idx - starts[wave][j];
             const typename Src::Item o = items[wave][j];
-            const unsigned key = active ? (unsigned)o.key(k) : 0u;
-            const unsigned long long peers = wave_match(key, active, nbits);
-            uint32_t pos = 0;
-            const int rank = lane_rank(peers);
-            if (active) pos = h[key] + (uint32_t)rank;
-            if (active && rank == 0) h[key] = pos + (uint32_t)__popcll(peers);
-            if (active) src.emit(slice, item0 + j, o, k, key, pos);
+            place(active, item0 + j, o, k, active ? (unsigned)o.key(k) : 0u);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
