@@ -19,7 +19,10 @@
 //  2 Huu', 3 Huv', 4 Hvv'   c2*H~uu, 2*c2*H~uv, c2*H~vv with c2 = -log2(e)/2 (exp2 argument)
 //  5 gu2, 6 gv2        2*g~u, 2*g~v
 //  7 Guu, 8 Guv2, 9 Gvv    G~uu, 2*G~uv, G~vv
-//  10 amp              rho*sqrt(2 pi / Q*)
+//  10 log2|amp|, amp = rho*sqrt(2 pi / Q*)
+// Three signs are marks: that of Huu' (<= 0) is flipped if the Gaussian is too narrow for the
+// splats' block polynomial, that of Guu (>= 0) if the polynomial needs its degree-5 terms, that of
+// Gvv (>= 0) if amp is negative; readers take -|Huu'|, |Guu| and |Gvv|.
 //  11 a00, 12 a01, 13 a11, 14 cx, 15 cy    the cut-off footprint as the ellipse
 //                      (p - c)^T A (p - c) <= 1 in pixel-index coordinates (A = 0: not an ellipse)
 // The per-pixel value is |e_ij| * amp * q^-1/2 * 2^(E' / q) with
@@ -55,6 +58,7 @@ struct DiagBlock {           // device copy of digs_diag plus internal totals
     unsigned int reserved[1];
     unsigned long long max_instances;   // largest `instances` of any call since the last reset
     unsigned long long stamp;           // DIAG_STAMP once the block has been cleared
+    unsigned long long counting;        // instances of the call under way; 0 between calls
 };
 
 // A workspace's diagnostics block counts as cleared only while it holds this stamp; the first call
@@ -73,6 +77,7 @@ __device__ __forceinline__ void diag_clear(DiagBlock *d)
     d->wide = 0;
     d->reserved[0] = 0;
     d->max_instances = 0;
+    d->counting = 0;
     d->stamp = DIAG_STAMP;
 }
 

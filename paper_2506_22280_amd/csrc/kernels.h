@@ -77,7 +77,7 @@ struct RenderArgs {
 };
 hipError_t render_forward_setup(const RenderArgs &a, hipStream_t s);   // a1-a4
 hipError_t render_forward_canonical(const RenderArgs &a, hipStream_t s);   // a1 (per Gaussian)
-hipError_t render_forward_views(const RenderArgs &a, hipStream_t s, bool begin = true);  // a2-a4
+hipError_t render_forward_views(const RenderArgs &a, hipStream_t s);       // a2-a4 (per view)
 // digs_project_fwd; with views_only the per-Gaussian stage in ws is taken as it is (it must come
 // from an earlier call on ws with the same Gaussians and lattice)
 int project_fwd_impl(const digs_geom *geom, const digs_grid *grid, const float *coef, int n,

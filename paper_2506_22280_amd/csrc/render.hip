@@ -11,15 +11,17 @@
 //                    (splat_poly.h), or, for Gaussians too narrow for it and short remainders,
 //                    lane = (Gaussian slot, column); every pixel is written once (no atomics)
 // Backward:
-//   k_splat_bwd      one lane per (list entry, 8x8 block) pair, looping over the block's 64 pixels
-//                    and accumulating 12 moment sums; one partial per instance (no atomics)
+//   k_splat_bwd      one lane per (list entry, 8x8 block) pair, over the block's 64 pixels by the
+//                    same polynomial, accumulating 12 moment sums; one partial per instance (no
+//                    atomics)
 //   k_tn_bwd         per Gaussian and chunk of views: sums the instance partials, runs the set-up
 //                    and warp adjoints per view and folds them into per-Gaussian sums; per-wave
 //                    partial sums of dL/dw
 //   k_gauss_reduce   per Gaussian, over the chunks in order: reduces to the canonical parameters
 //                    (with the second-derivative term) and emits the sources of dL/dcoef
-//   k_cell_*         stable radix sort of the Gaussians by lattice cell
-//   k_coef_grad      each control point gathers from the Gaussians of its 4x4x4 cells
+//   CellSrc, RadixSrc, k_cell_start   stable radix sort of the Gaussians by lattice cell (bin.h)
+//   k_coef_grad      control points gather from the Gaussians of their 4x4x4 cells, a product on
+//                    the FP32 matrix cores
 //
 // The exact line integral of one Gaussian (Eq. 2 along the ray of Eq. 1, the quantity that
 // Eq. 4 approximates) is evaluated in a whitened, cancellation-free form: with W = M^-1,
@@ -45,18 +47,23 @@
 
 // ------------------------------------------------------------------------------------------
 // Diagnostics and small fills
-__device__ __forceinline__ void diag_begin(DiagBlock *d, unsigned long long cap,
-                                           uint32_t *cnt_last)
+// A call's diagnostics: the set-up counts its instances in `counting`; the placement of the tile
+// lists, the next kernel but two, publishes them and leaves 0 for the next call. The per-Gaussian
+// stage, without which no view is rendered on a workspace, begins it.
+__device__ __forceinline__ void diag_begin(DiagBlock *d)
 {
     if (d->stamp != DIAG_STAMP) diag_clear(d);
-    d->instances = 0;
-    d->capacity = cap;
-    *cnt_last = 0;
+    d->counting = 0;
 }
 
-__global__ void k_diag_begin(DiagBlock *d, unsigned long long cap, uint32_t *cnt_last)
+__device__ __forceinline__ void diag_publish(DiagBlock *d, unsigned long long cap)
 {
-    diag_begin(d, cap, cnt_last);
+    const unsigned long long n = d->counting;
+    d->counting = 0;
+    d->instances = n;
+    d->capacity = cap;
+    if (n > cap) d->overflow = 1u;
+    if (n > d->max_instances) d->max_instances = n;
 }
 
 __global__ void k_fill_f32(float *p, size_t count, float v)
@@ -107,10 +114,10 @@ __global__ __launch_bounds__(256) void k_ffd_canonical(DevGrid g, const float *_
                                                        const float *__restrict__ rho,
                                                        const uint32_t *__restrict__ order,
                                                        float *__restrict__ uv,
-                                                       float *__restrict__ gs, DiagBlock *diag,
-                                                       unsigned long long cap, uint32_t *cnt_last)
+                                                       float *__restrict__ gs,
+                                                       DiagBlock *__restrict__ diag)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) diag_begin(diag, cap, cnt_last);
+    if (blockIdx.x == 0 && threadIdx.x == 0) diag_begin(diag);
     // four lanes per Gaussian: lane `part` takes the stencil's z index part, and the four partial
     // sums are added in a fixed order. The control points the workgroup's 64 Gaussians reach
     // (neighbours in cell order) are staged in LDS first.
@@ -556,7 +563,7 @@ __global__ __launch_bounds__(256) void k_setup(DevGeom G, int n, int T,
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long tot = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-        if (tot) atomicAdd(&diag->instances, tot);
+        if (tot) atomicAdd(&diag->counting, tot);
     }
 }
 
@@ -650,12 +657,7 @@ struct TileSrc {
         it.fe.ell = false;
         return it;
     }
-    // the call's instances, which the set-up has counted, against the capacity
-    __device__ void begin_fill() const
-    {
-        if (diag->instances > diag->capacity) diag->overflow = 1u;
-        if (diag->instances > diag->max_instances) diag->max_instances = diag->instances;
-    }
+    __device__ void begin_fill() const { diag_publish(diag, (unsigned long long)cap); }
     __device__ void prepare(int t, int item, Item &it) const
     {
         const float4 *r = rec + ((size_t)t * items + item) * 4;
@@ -2747,12 +2749,6 @@ static hipError_t cell_sort(const RenderArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-// The last of the tile lists' counts, one past every list: zero, so that its scan is the total
-static uint32_t *count_end(const RenderArgs &a)
-{
-    return WS(a, cnt, uint32_t *) + (size_t)a.T * a.geom.ntiles * a.L.nblk;
-}
-
 // The per-Gaussian stage (cell order, the Gaussians gathered into it, the FFD at the canonical
 // means): a function of the Gaussians and the lattice alone, shared by every view of a call.
 hipError_t render_forward_canonical(const RenderArgs &a, hipStream_t s)
@@ -2767,7 +2763,7 @@ hipError_t render_forward_canonical(const RenderArgs &a, hipStream_t s)
                            dim3(256), 0, s, a.grid,
                            a.coef, a.basis, a.n, a.mu, a.scale, a.quat, a.rho,
                            WS(a, order, const uint32_t *), WS(a, uv, float *), WS(a, gsort, float *),
-                           WS(a, diag, DiagBlock *), (unsigned long long)a.L.cap, count_end(a));
+                           WS(a, diag, DiagBlock *));
     }
     return hipGetLastError();
 }
@@ -2776,7 +2772,7 @@ hipError_t render_forward_setup(const RenderArgs &a, hipStream_t s)
 {
     hipError_t e = render_forward_canonical(a, s);
     if (e != hipSuccess) return e;
-    return render_forward_views(a, s, false);
+    return render_forward_views(a, s);
 }
 
 // The tile lists of the call's (view, Gaussian) instances, binned for a TW x TH tile shape.
@@ -2798,17 +2794,11 @@ static hipError_t bin_tiles(const RenderArgs &a, uint32_t *cnt, size_t cnt_elems
 }
 
 // The per-view stages: the warp and projected records, instance offsets and the tile lists.
-// begin: without the per-Gaussian stage before it, which otherwise begins the diagnostics.
-hipError_t render_forward_views(const RenderArgs &a, hipStream_t s, bool begin)
+hipError_t render_forward_views(const RenderArgs &a, hipStream_t s)
 {
     hipError_t e;
     const size_t cnt_elems = (size_t)a.T * a.geom.ntiles * a.L.nblk;
     uint32_t *cnt = WS(a, cnt, uint32_t *);
-    if (begin) {
-        hipLaunchKernelGGL(k_diag_begin, dim3(1), dim3(1), 0, s, WS(a, diag, DiagBlock *),
-                           (unsigned long long)a.L.cap, count_end(a));
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
     {
         ProfScope ps(PS_SETUP, s);
         switch (a.grid.R) {

@@ -10,8 +10,8 @@
 //
 // phi: each Gaussian's cut-off box (Mahalanobis radius r_c per axis) is binned into 8x8x8-voxel
 // bricks by emitting (brick, Gaussian) pairs in Gaussian order and sorting them stably by brick;
-// one workgroup per brick then sums its Gaussians over its 512 voxels in that fixed order and
-// writes every voxel once.
+// one workgroup per brick then sums its Gaussians over its 512 voxels, a quarter of the list per
+// wave, in that fixed order and writes every voxel once.
 #include <math.h>
 #include <string.h>
 
