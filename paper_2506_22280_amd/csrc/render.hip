@@ -2181,7 +2181,7 @@ __device__ __forceinline__ float quad_lane(float v, int l)
 // derivatives after the other's, it took 30 us for 4k Gaussians and 16 views (now 18), 143 for 200k
 // and 64 (107), 377 for 500k, R = 4 (288; 350 without the cap), 31 for 80k, R = 2 (28).
 template <int NR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, NR <= 3 ? 3 : 2)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, NR == 1 ? 4 : NR <= 3 ? 3 : 2)))
 void k_gauss_reduce(
     DevGrid grid, int n, int nch, const float *__restrict__ coef, const float *__restrict__ gpar,
     const float *__restrict__ uv, const float *__restrict__ tacc,
@@ -2688,6 +2688,90 @@ __global__ __launch_bounds__(WAVES *DIGS_WAVE) void k_coef_grad(
     }
 }
 
+// The same for rank 1, whose three components would leave most of a matrix tile empty while a row is
+// only 72 bytes: a wave per control point, the lanes taking the Gaussians of its cells 64 at a time,
+// their sums reduced over the wave in a fixed order (288k Gaussians, 29^3 points: 196 us, by blocks
+// 239; rank 2 gains by blocks, 72 -> 61 us with 80k).
+__global__ __launch_bounds__(256) void k_coef_grad_rank1(
+    DevGrid g, const float *__restrict__ gq, int gq_stride,
+    const uint32_t *__restrict__ cell_start, float *__restrict__ g_coef)
+{
+    const int idx = blockIdx.x * 4 + threadIdx.x / DIGS_WAVE;
+    const int lane = lane_id();
+    const int npts = g.nx * g.ny * g.nz;
+    if (idx >= npts) return;
+    const int i = idx % g.nx, j = (idx / g.nx) % g.ny, k = idx / (g.nx * g.ny);
+    float acc[3] = {0.0f, 0.0f, 0.0f};
+    const int lx = (i == 0) ? -2 : i - 2, hx = (i == g.nx - 1) ? g.nx + 1 : i + 1;
+    const int ly = (j == 0) ? -2 : j - 2, hy = (j == g.ny - 1) ? g.ny + 1 : j + 1;
+    const int lz = (k == 0) ? -2 : k - 2, hz = (k == g.nz - 1) ? g.nz + 1 : k + 1;
+    const float ihx = 1.0f / g.hx, ihy = 1.0f / g.hy, ihz = 1.0f / g.hz;
+    // The support's cell rows (cz, cy), at most 5 x 5, each a contiguous range of Gaussians in
+    // cell order: lane r < nrows holds row r's range, and the rows' Gaussians are taken 64 at a
+    // time over all rows together (a row holds only a few Gaussians).
+    const int nry = hy - ly + 1, nrows = (hz - lz + 1) * nry;
+    uint32_t rb = 0, rlen = 0;
+    if (lane < nrows) {
+        const int cz = lz + lane / nry, cy = ly + lane % nry;
+        const uint32_t row = ((uint32_t)(cz + 2) * (g.ny + 4) + (cy + 2)) * (g.nx + 4);
+        rb = cell_start[row + (lx + 2)];
+        rlen = cell_start[row + (hx + 2) + 1] - rb;
+    }
+    // inclusive prefix sum of the row lengths over lanes 0..31 (nrows <= 25)
+    uint32_t incl = rlen;
+#pragma unroll
+    for (int off = 1; off < 32; off <<= 1) {
+        const uint32_t y = __shfl_up(incl, off, DIGS_WAVE);
+        if (lane >= off) incl += y;
+    }
+    const uint32_t total = __shfl(incl, 31, DIGS_WAVE);
+    for (uint32_t q0 = 0; q0 < total; q0 += DIGS_WAVE) {
+        // the row of flattened index q: the first lane whose inclusive sum exceeds q (the
+        // shuffles run with every lane active; lanes past the end then skip the work)
+        const uint32_t q = q0 + (uint32_t)lane;
+        int row = 0;
+#pragma unroll
+        for (int step = 16; step >= 1; step >>= 1)
+            if (__shfl(incl, row + step - 1, DIGS_WAVE) <= q) row += step;
+        row = min(row, 31);
+        const uint32_t p = __shfl(rb, row, DIGS_WAVE) + q -
+                           (__shfl(incl, row, DIGS_WAVE) - __shfl(rlen, row, DIGS_WAVE));
+        if (q >= total) continue;
+        const float *o = gq + (size_t)p * gq_stride;
+        // the Gaussian's (clamped) cell
+        int cx = __float_as_int(o[0]);
+        const int cy = __float_as_int(o[1]), cz = __float_as_int(o[2]);
+        cx -= cx > CG_BAD / 2 ? CG_BAD : 0;
+        float B[4], dB[4];
+        float wx = 0.f, dwx = 0.f, wy = 0.f, dwy = 0.f, wz = 0.f, dwz = 0.f;
+        bspline4(o[3], B);
+        bspline4_d(o[3], dB);
+#pragma unroll
+        for (int l = 0; l < 4; ++l)
+            if (clampi(cx - 1 + l, g.nx) == i) { wx += B[l]; dwx += dB[l]; }
+        bspline4(o[4], B);
+        bspline4_d(o[4], dB);
+#pragma unroll
+        for (int l = 0; l < 4; ++l)
+            if (clampi(cy - 1 + l, g.ny) == j) { wy += B[l]; dwy += dB[l]; }
+        bspline4(o[5], B);
+        bspline4_d(o[5], dB);
+#pragma unroll
+        for (int l = 0; l < 4; ++l)
+            if (clampi(cz - 1 + l, g.nz) == k) { wz += B[l]; dwz += dB[l]; }
+        const float w0 = wx * wy * wz, w1 = dwx * ihx * wy * wz, w2 = wx * dwy * ihy * wz,
+                    w3 = wx * wy * dwz * ihz;
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            acc[a] += w0 * o[6 + a] + w1 * o[9 + a] + w2 * o[12 + a] + w3 * o[15 + a];
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float v = wave_sum(acc[a]);
+        if (lane == 0) g_coef[(size_t)idx * 3 + a] = v;
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // host orchestration
 template <int NR>
@@ -2986,14 +3070,18 @@ static hipError_t backward_dispatch(const RenderArgs &a, float *g_mu, float *g_s
         // done sooner (20k Gaussians, 16^3 points, 256 blocks: 46 us with 8, 40 with 16), else 8, so
         // that a CU holds several blocks at different stages. Two column tiles leave registers for
         // 8 only.
-        if (NR <= 5 && plane * a.grid.nz < 1000)
-            hipLaunchKernelGGL((k_coef_grad<NR, (NR <= 5 ? 16 : 8)>), blocks, dim3(1024), 0, s, a.grid,
-                           WS(a, gq, const float *), a.L.gq_stride,
-                           WS(a, cell_start, const uint32_t *), g_coef);
+        const float *gq = WS(a, gq, const float *);
+        const uint32_t *cells = WS(a, cell_start, const uint32_t *);
+        if constexpr (NR == 1)
+            hipLaunchKernelGGL(k_coef_grad_rank1,
+                               dim3((a.grid.nx * a.grid.ny * a.grid.nz + 3) / 4), dim3(256), 0, s,
+                               a.grid, gq, a.L.gq_stride, cells, g_coef);
+        else if (NR <= 5 && plane * a.grid.nz < 1000)
+            hipLaunchKernelGGL((k_coef_grad<NR, (NR <= 5 ? 16 : 8)>), blocks, dim3(1024), 0, s,
+                               a.grid, gq, a.L.gq_stride, cells, g_coef);
         else
-            hipLaunchKernelGGL((k_coef_grad<NR, 8>), blocks, dim3(512), 0, s, a.grid,
-                           WS(a, gq, const float *), a.L.gq_stride,
-                           WS(a, cell_start, const uint32_t *), g_coef);
+            hipLaunchKernelGGL((k_coef_grad<NR, 8>), blocks, dim3(512), 0, s, a.grid, gq,
+                               a.L.gq_stride, cells, g_coef);
         e = hipGetLastError();
     }
     return e;
