@@ -330,20 +330,6 @@ __device__ __forceinline__ bool footprint_box(const DevGeom &G, const SetupFwd &
     return true;
 }
 
-// Bound on the error, in units of the Gaussian's peak, of the exponent taken over an 8x8 block as a
-// quartic (splat_poly.h), wherever the footprint reaches: k bounds |q / q00 - 1| over a block whose
-// centre lies within 4 pixels of the footprint's box, rho^2 = 24.5 times the trace of H (at least
-// its largest eigenvalue).
-__device__ __forceinline__ float poly_error(const SetupFwd &f, const Footprint &fp)
-{
-    const float ru = fp.hu + 4.0f, rv = fp.hv + 4.0f;
-    const float gu = 2.0f * (fabsf(f.gu) + f.Guu * ru + fabsf(f.Guv) * rv);
-    const float gv = 2.0f * (fabsf(f.gv) + f.Gvv * rv + fabsf(f.Guv) * ru);
-    const float k = 3.5f * (gu + gv) + 12.25f * (f.Guu + 2.0f * fabsf(f.Guv) + f.Gvv);
-    const float rho2 = 24.5f * (f.Huu + f.Hvv);
-    return POLY_HL * (rho2 + 0.5f) * k * k * k;
-}
-
 // The cut-off ellipse by horizontal chords: at y = cy + dy the chord is
 // x in cx - s dy -+ sqrt((1 - D dy^2) ia), |dy| <= ry; its leftmost point is at dy = ryl and its
 // rightmost at dy = -ryl (1 carries a slack of 1e-5). ell is false for a footprint that is not an
@@ -509,7 +495,10 @@ __global__ __launch_bounds__(256) void k_setup(DevGeom G, int n, int T,
         if (ok) {
             const bool ellipse = footprint_box(G, f, cull, x0, x1, y0, y1, fp);
             if (!ellipse && valid) atomicAdd(&diag->wide, 1u);
-            const float err = poly_error(f, fp);
+            // (a block that the footprint meets has its centre within 4 pixels of the box)
+            const float err = poly_error(f.Huu, f.Huv, f.Hvv, f.gu, f.gv, f.Guu, f.Guv, f.Gvv,
+                                         fabsf(fp.cx - f.us) + fp.hu + 4.0f,
+                                         fabsf(fp.cy - f.vs) + fp.hv + 4.0f);
             plain = ellipse && err <= POLY_PLAIN;
             fold = ellipse && err <= POLY_FOLD;
         }

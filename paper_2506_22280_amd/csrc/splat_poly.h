@@ -8,17 +8,18 @@
 // and log2 q to second order. A pixel then costs 2.5 multiply-adds and one exp2 (two columns at
 // +-s share the even and odd parts) instead of a reciprocal square root, an exp2 and seven others.
 //
-// The series is cut after total degree 4. With k the largest |q/q00 - 1| over the block and rho
-// the block's half diagonal in standard deviations of the Gaussian, what is left out changes a
-// pixel's value by less than 0.72 (rho^2 + 1/2) k^3 of the Gaussian's peak (0.72 = log2(e)/2; its
-// root mean square over the phantoms of synth.py is a tenth of that, at detector pitches of 0.4 to
-// 6 mm). Folding the degree-5 terms into the lower ones (each power replaced by its closest lower
-// polynomial over the block's pixel positions, the log to third order) leaves an eighth. The set-up
-// evaluates the bound per (view, Gaussian) and marks the record: up to POLY_PLAIN the plain series
-// is as close as the FP32 evaluation by forward differences, up to POLY_FOLD the folded one and the
-// moments taken with it are, and records above that are evaluated directly. (With 1.2e-5 and 4e-5
-// for POLY_FOLD single rotation gradients of sub-pixel Gaussians, out of 288k, moved by 1.5e-3 of
-// their root mean square; with 4e-6 by 4e-4, with no polynomial and another order of sums by 3e-4.)
+// The series is cut after total degree 4. With l and c the largest linear and quadratic part of
+// q / q00 - 1 over the block, and rho the largest distance of its pixels from its centre in standard
+// deviations of the Gaussian, what is left out changes a pixel's value by at most about
+// (rho^2 + 1/2) (l^3 + 2 l c + c^2) / 2 of the Gaussian's peak (poly_error, derived there): the
+// quadratic part is small like l, but takes up two degrees. The set-up evaluates the bound per
+// (view, Gaussian) and marks the record: the plain series up to POLY_PLAIN, direct evaluation above
+// POLY_FOLD, and between them the degree-5 terms folded into the lower ones (each power replaced by
+// its closest lower polynomial over the block's pixel positions, the log to third order), which
+// leaves an eighth of the value's error. The moments keep the order of the plain series, and with
+// that half the bound, relative to the amplitude's gradient, in the gradients of orientation and
+// scale; hence the limit on folded records, at the error of the FP32 evaluation by forward
+// differences (Gaussians of one to four pixels: 1e-6 to 4e-6).
 #pragma once
 
 #include "common.h"
@@ -40,6 +41,29 @@ struct BlockPoly {
     float iq, lrs;                      // 1 / q00, -log2(q00) / 2
     float du, dv;                       // the block's centre less the footprint's
 };
+
+// Bound, in units of the Gaussian's peak, on the error of a pixel's value by the plain series over any
+// block whose centre lies within (ru, rv) pixels of the projected mean: H, g and G the record's
+// quadratic forms (q = 1 + 2 g.d + d^T G d). With L and C the linear and quadratic part of q / q00 - 1
+// (|L| <= l, |C| <= c), y_n the part of degree n of E/q and A the distance of the block's centre from
+// the mean in deviations, dividing out the series leaves, over 1 + L + C and to second order in c,
+//   (-L^3 + 2 L C + C^2) y2 + C^2 y1  and, of the logarithm, (-L C + L^3/3 - C^2/2) / 2,
+// in natural units, where |y1| <= A rho and |y2| <= rho^2 / 2 to first order; the pixel's own value, at
+// most exp(-(A - rho)^2 / 2) of the peak, keeps its product with A below rho + 0.61. 1/q00 <= iq, as
+// G is positive. NaN or infinite where q may come near 0. Measured against FP64 over Gaussians of
+// 0.15 to 6 pixels, aspects up to 9 and pitches of 0.4 to 11 mm, the worst error is 0.93 of it.
+__host__ __device__ inline float poly_error(float Huu, float Huv, float Hvv, float gu, float gv,
+                                            float Guu, float Guv, float Gvv, float ru, float rv)
+{
+    const float q = 1.0f - 2.0f * (fabsf(gu) * ru + fabsf(gv) * rv);
+    const float iq = q > 0.5f ? 1.0f / q : INFINITY;
+    const float l = 7.0f * iq *
+                    (fabsf(gu) + fabsf(gv) + Guu * ru + fabsf(Guv) * (ru + rv) + Gvv * rv);
+    const float c = 12.25f * iq * (Guu + 2.0f * fabsf(Guv) + Gvv);
+    const float rho2 = 12.25f * iq * (Huu + 2.0f * fabsf(Huv) + Hvv);
+    return 0.5f * (rho2 + 0.5f) * (l * (l * l + 2.0f * c) + c * c) +
+           (rho2 + 0.61f * sqrtf(rho2)) * c * c;
+}
 
 // The record's marks: Guu >= +0 is stored negative if the plain series is not enough, Huu' <= -0 is
 // stored positive if the folded one is not either.
