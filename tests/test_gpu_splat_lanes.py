@@ -1,17 +1,53 @@
-"""The exact model's forward splat by the block polynomial for Gaussians on the corner of a block, where
-the series is worst, against the same Gaussians by forward differences (lists cut into slices too short
-for the polynomial)."""
+"""The exact model's splats where lists are long enough for the forward's block polynomial (one slice,
+over a thousand entries a list): amplitudes of both signs and zero, records of the plain, the folded
+and the direct form, direct ones set aside from groups of the others, more Gaussians that meet one
+half of a block than are kept apart, and Gaussians on the corner of a block, where the series is worst.
+
+Forward bar, per unit of the image of the Gaussians' magnitudes: the limit on folded records (4e-6) and
+the FP32 evaluation (2e-6 for Gaussians of a pixel or more); the footprints reach 7 deviations, which
+leaves out 2e-11. Gradients: the suite's bars."""
+import math
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
-from gpu_helpers import dev
+from gpu_helpers import check_grads, dev
 from paper_2506_22280_amd import _lib
+from splat_ref import bound, reach, record
 
 pytestmark = pytest.mark.gpu
 
-CULL = 7.0
+CULL, PLAIN, FOLD = 7.0, 2.0e-6, 4.0e-6
+# deviations in pixels at the mean, aspect, pitch (mm); the wanted share of folded and direct records
+SCENES = {
+    "plain": dict(pitch=0.8, size=(1.5, 4.0), aspect=2.0, folded=(0.0, 0.01), direct=(0.0, 0.01)),
+    "folded": dict(pitch=4.6, size=(4.0, 5.0), aspect=1.1, folded=(0.5, 1.0), direct=(0.0, 0.1)),
+    "mixed": dict(pitch=1.6, size=(1.0, 3.0), aspect=2.0, folded=(0.02, 1.0), direct=(0.03, 0.1)),
+    "halves": dict(pitch=0.4, size=(2.5, 4.0), flat=0.2, folded=(0.0, 0.01), direct=(0.0, 0.01)),
+}
+
+
+def _scene(name, n, nu, nv):
+    s = SCENES[name]
+    rng = np.random.default_rng(len(name))
+    pitch = s["pitch"]
+    px = pitch * 1000.0 / 1500.0    # a pixel at the axis (mm)
+    half = np.array([0.5 * nu, 0.5 * nu, 0.5 * nv]) * px
+    mu = rng.uniform(-1, 1, (3, n)) * half[:, None]
+    mu[1] = np.clip(mu[1], -100, 100)
+    scale = px * np.exp(rng.uniform(*np.log(s["size"]), n)) * np.ones((3, 1))
+    quat = rng.standard_normal((4, n))
+    if "flat" in s:                 # thin along the detector's columns
+        scale[2] *= s["flat"]
+        quat = np.array([1.0, 0.0, 0.0, 0.0])[:, None] * np.ones(n)
+    else:
+        scale = scale * np.exp(rng.uniform(-0.5, 0.5, (3, n)) * math.log(s["aspect"]))
+    rho = rng.uniform(0.2, 1.0, n) / scale[0]
+    rho[rng.random(n) < 0.2] *= -1.0
+    rho[::50] = 0.0
+    return mu, scale, quat, rho, pitch
 
 
 def _still(mu, scale, quat, rho, pitch, angles, nu, nv):
@@ -39,6 +75,32 @@ def _render(geom, grid, ins, G=None, entries=None, **tuning):
     tiles = ((geom["nu"] + 15) // 16) * ((geom["nv"] + 15) // 16)
     assert diag["instances"] >= (entries or 1000 * T * tiles)
     return proj.cpu().numpy(), out
+
+
+@pytest.mark.parametrize("name", list(SCENES))
+def test_long_lists_match_oracle(name):
+    print("case: long lists, %s records" % name, flush=True)
+    nu, nv, angles = 40, 24, np.array([0.3, 1.9])
+    mu, scale, quat, rho, pitch = _scene(name, 6000, nu, nv)
+    share = np.zeros(2)
+    for a in angles:
+        f = record(mu, scale, quat, pitch, a)
+        ok, _, _, ru, rv = reach(f, CULL)
+        b = np.where(ok, bound(f, ru, rv), np.inf)
+        share += np.array([((b > PLAIN) & (b <= FOLD)).mean(), (b > FOLD).mean()]) / len(angles)
+    print("folded %.3f, direct %.3f" % tuple(share), flush=True)
+    for got, want in zip(share, (SCENES[name]["folded"], SCENES[name]["direct"])):
+        assert want[0] <= got <= want[1]
+    geom, grid, ins = _still(mu, scale, quat, rho, pitch, angles, nu, nv)
+    G = np.random.default_rng(1).normal(0, 1, (2, nv, nu)).astype(np.float32)
+    proj, out = _render(geom, grid, ins, G)
+    ref = oracle.project(geom, grid, *ins)
+    size = oracle.project(geom, grid, *ins[:4], np.abs(ins[4]), *ins[5:])
+    err = float((np.abs(proj - ref)).max() / size.max())
+    print("forward max err / max magnitude %.2e" % err, flush=True)
+    assert err <= 6e-6
+    gref = oracle.project_bwd(geom, grid, *ins, grad_proj=G)
+    check_grads({k: out[k] for k in gref}, gref)
 
 
 # next to the axis: round footprints, whose q has hardly a gradient but a curvature. The plain series
