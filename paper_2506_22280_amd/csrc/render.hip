@@ -1072,6 +1072,12 @@ __device__ __forceinline__ float splat_fwd_block(const float4 *__restrict__ rt,
                     if (dir) q2[n2 + lane_rank(dm)] = ent;
                     n2 += __popcll(dm);
                     wave_sync_lds();
+                    // (their lanes idle with an empty record: their own series need not be
+                    // finite, and would reach every pixel of the block)
+                    if (mark_direct(r0)) {
+                        r0 = r1 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                        r2 = idle_rec2();
+                    }
                     if (n2 >= DIGS_WAVE) {
                         splat_fwd_cols(rt, q2, 0, n2, ~0, lane, fx, fy, accc);
                         n2 = 0;

@@ -124,3 +124,20 @@ def test_gaussians_on_a_block_corner(pitch, size):
     print("forward max err / max %.2e, by columns %.2e, between them %.2e" % tuple(err), flush=True)
     # the limit on folded records, and at most 60 additions in turn on each side
     assert err[2] <= 4e-6 + 60 * 2.0 ** -24
+
+
+def test_a_vanishing_denominator_stays_with_its_gaussian():
+    """Wide, thin sheets among ordinary Gaussians, level with the source's orbit and below it: on the
+    rays of the row of block centres at the middle of the detector, which run parallel to them, their
+    denominator vanishes, while their values are zero there."""
+    print("case: thin level sheets among plain records", flush=True)
+    nu, nv, angles = 40, 24, np.array([0.3])
+    mu, scale, quat, rho, pitch = _scene("plain", 6000, nu, nv)
+    mu[2, ::150], scale[:, ::150] = -20.0, np.array([400.0, 400.0, 1e-4])[:, None]
+    quat[:, ::150], rho[::150] = np.array([1.0, 0.0, 0.0, 0.0])[:, None], 1.0
+    geom, grid, ins = _still(mu, scale, quat, rho, pitch, angles, nu, nv)
+    proj, _ = _render(geom, grid, ins)
+    ref = oracle.project(geom, grid, *ins)
+    size = oracle.project(geom, grid, *ins[:4], np.abs(ins[4]), *ins[5:])
+    assert np.isfinite(proj).all()
+    assert np.abs(proj - ref).max() / size.max() <= 6e-6
