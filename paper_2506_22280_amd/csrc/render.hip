@@ -499,8 +499,9 @@ __global__ __launch_bounds__(256) void k_setup(DevGeom G, int n, int T,
             const float err = poly_error(f.Huu, f.Huv, f.Hvv, f.gu, f.gv, f.Guu, f.Guv, f.Gvv,
                                          fabsf(fp.cx - f.us) + fp.hu + 4.0f,
                                          fabsf(fp.cy - f.vs) + fp.hv + 4.0f);
-            plain = ellipse && err <= POLY_PLAIN;
-            fold = ellipse && err <= POLY_FOLD;
+            const bool poly = ellipse && poly_rho2(f.Huu, f.Huv, f.Hvv) <= POLY_RHO2;
+            plain = poly && err <= POLY_PLAIN;
+            fold = poly && err <= POLY_FOLD;
         }
         uint32_t count = 0;
         int4 rr = make_int4(1, 0, 0, 0);

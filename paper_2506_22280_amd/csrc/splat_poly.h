@@ -19,13 +19,18 @@
 // leaves an eighth of the value's error. The moments keep the order of the plain series, and with
 // that half the bound, relative to the amplitude's gradient, in the gradients of orientation and
 // scale; hence the limit on folded records, at the error of the FP32 evaluation by forward
-// differences (Gaussians of one to four pixels: 1e-6 to 4e-6).
+// differences (Gaussians of one to four pixels: 1e-6 to 4e-6). Evaluated directly as well are
+// Gaussians with rho^2 above POLY_RHO2 (0.6 of a pixel if round): the series is a small difference of
+// terms of the order of rho^2 there, and its FP32 rounding exceeds that of the forward differences
+// (largest error of an image, pitch 0.5 mm, aspects up to 3: 0.3 pixels 1.3e-5 against 5.8e-6 of its
+// maximum, 0.5 pixels 6.7e-6 against 3.2e-6, 0.6 and 0.8 pixels the same).
 #pragma once
 
 #include "common.h"
 
 #define POLY_PLAIN 2.0e-6f
 #define POLY_FOLD 4.0e-6f
+#define POLY_RHO2 64.0f
 #define POLY_HL 0.72134752044448170f   // log2(e) / 2
 
 // Index of s^i t^j (i + j <= 4) among the 15 coefficients and moments.
@@ -41,6 +46,12 @@ struct BlockPoly {
     float iq, lrs;                      // 1 / q00, -log2(q00) / 2
     float du, dv;                       // the block's centre less the footprint's
 };
+
+// Largest squared distance of a block's pixels from its centre in deviations of the Gaussian
+__host__ __device__ inline float poly_rho2(float Huu, float Huv, float Hvv)
+{
+    return 12.25f * (Huu + 2.0f * fabsf(Huv) + Hvv);
+}
 
 // Bound, in units of the Gaussian's peak, on the error of a pixel's value by the plain series over any
 // block whose centre lies within (ru, rv) pixels of the projected mean: H, g and G the record's
@@ -60,7 +71,7 @@ __host__ __device__ inline float poly_error(float Huu, float Huv, float Hvv, flo
     const float l = 7.0f * iq *
                     (fabsf(gu) + fabsf(gv) + Guu * ru + fabsf(Guv) * (ru + rv) + Gvv * rv);
     const float c = 12.25f * iq * (Guu + 2.0f * fabsf(Guv) + Gvv);
-    const float rho2 = 12.25f * iq * (Huu + 2.0f * fabsf(Huv) + Hvv);
+    const float rho2 = iq * poly_rho2(Huu, Huv, Hvv);
     return 0.5f * (rho2 + 0.5f) * (l * (l * l + 2.0f * c) + c * c) +
            (rho2 + 0.61f * sqrtf(rho2)) * c * c;
 }
