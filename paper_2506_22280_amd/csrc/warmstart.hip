@@ -6,10 +6,13 @@
 // warm start is a small MLP (downsampled projection and gantry angle in, w_t out) whose matrix
 // products run on the gfx950 matrix cores: BF16 operands, FP32 accumulation (k_gemm_bf16), with
 // FP32 master weights updated by Adam.
+#include <algorithm>
+
 #include "kernels.h"
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // ------------------------------------------------------------------------------------------
 // C[M][N] = epilogue(A . B) with op(A) [M][K] and op(B) [K][N] read from FP32 memory, rounded to
@@ -24,7 +27,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // the loop. Column TN * (l % 16) + j of the wave's tile is column l % 16 of its j-th matrix, which
 // makes a lane's TN columns adjacent in memory. KW waves of a workgroup share a tile, wave w
 // taking the 32-wide steps w, w + KW, ... of K, and their sums are added in wave order; with
-// KW == 1 the workgroup's four waves take neighbouring tiles.
+// KW == 1 the workgroup's four waves take neighbouring tiles. Tiles go along the rows of C, or down its
+// columns where those are more and the rows either many or one row of tiles enough to fill the chip: B
+// is then used again while it is in the caches (256x65536x1024: 568 us along, 310 down; 4096x8192x4096:
+// 2549 and 2006, with A transposed 3575 and 2151; but 64x16384x512: 13 and 22).
 // Measured against 64x64 tiles of C staged through LDS, a workgroup each (M x N x K): 267 -> 9 us
 // (32x256x4098), 558 -> 21 (256x512x4098), 50 -> 4 (186x128x578), 20 -> 3 (32x256x256), gradients of
 // the weights 7.3 -> 4.4 (4098x256x32) and 41 -> 17 (4098x512x256).
@@ -92,7 +98,9 @@ __global__ __launch_bounds__(KW == 16 ? 1024 : 256) void k_gemm_bf16(
     const int ntn = (N + COLS - 1) / COLS, ntm = (M + GT_ROWS - 1) / GT_ROWS;
     const int64_t tile = (int64_t)blockIdx.x * NT + (KW == 1 ? wave : 0);
     const bool have = tile < (int64_t)ntn * ntm;   // (false only with KW == 1)
-    const int m0 = have ? (int)(tile / ntn) * GT_ROWS : 0, n0 = have ? (int)(tile % ntn) * COLS : 0;
+    const bool down = N > M && (M >= 1024 || N >= 65536);
+    const int m0 = have ? (int)(down ? tile % ntm : tile / ntn) * GT_ROWS : 0;
+    const int n0 = have ? (int)(down ? tile / ntm : tile % ntn) * COLS : 0;
     const int kw = KW == 1 ? 0 : wave, kl = 8 * (lane >> 4);
     const float *pa[1], *pb[TN];
     const int row = min(m0 + (lane & 15), M - 1);
@@ -186,6 +194,68 @@ __global__ __launch_bounds__(KW == 16 ? 1024 : 256) void k_gemm_bf16(
                 for (int w = 1; w < KW; ++w) v[t] += e[w * GT_ROWS * COLS];
             }
             store(threadIdx.x >> 4, threadIdx.x & 15, v);
+        }
+    }
+}
+
+// The same from tiles of 64 x 64, a workgroup each (four waves, a 32 x 32 block each on
+// v_mfma_f32_32x32x16_bf16), K staged through LDS 32 at a time: each operand is read once per 64 rows
+// or columns of C, coalesced also where K is the contiguous index.
+#define GT_TILE 64
+#define GT_LDS 40   // bf16 per LDS row: 80 bytes, so every 8-element fragment is 16-byte aligned
+
+template <bool TA, bool TB>
+__global__ __launch_bounds__(256) void k_gemm_bf16_staged(
+    int M, int N, int K, const float *__restrict__ A, int lda, const float *__restrict__ B, int ldb,
+    float *__restrict__ C, int ldc, const float *__restrict__ bias,
+    const float *__restrict__ gate, int relu, int accumulate)
+{
+    __shared__ __attribute__((aligned(16))) __bf16 As[GT_TILE * GT_LDS];
+    __shared__ __attribute__((aligned(16))) __bf16 Bs[GT_TILE * GT_LDS];
+    const int m0 = blockIdx.y * GT_TILE, n0 = blockIdx.x * GT_TILE;
+    const int tid = threadIdx.x, wave = tid / DIGS_WAVE, lane = lane_id();
+    const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    for (int k0 = 0; k0 < K; k0 += GT_K) {
+        for (int e = tid; e < GT_TILE * GT_K; e += 256) {
+            const int r = TA ? e % GT_TILE : e / GT_K, c = TA ? e / GT_TILE : e % GT_K;
+            const int m = m0 + r, k = k0 + c;
+            float v = 0.0f;
+            if (m < M && k < K) v = TA ? A[(size_t)k * lda + m] : A[(size_t)m * lda + k];
+            As[r * GT_LDS + c] = (__bf16)v;
+        }
+        for (int e = tid; e < GT_TILE * GT_K; e += 256) {
+            const int r = TB ? e / GT_K : e % GT_TILE, c = TB ? e % GT_K : e / GT_TILE;
+            const int nn = n0 + r, k = k0 + c;
+            float v = 0.0f;
+            if (nn < N && k < K) v = TB ? B[(size_t)nn * ldb + k] : B[(size_t)k * ldb + nn];
+            Bs[r * GT_LDS + c] = (__bf16)v;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < GT_K; s += 16) {
+            const int kk = s + 8 * (lane >> 5);
+            const bf16x8 a = *(const bf16x8 *)&As[(wm + (lane & 31)) * GT_LDS + kk];
+            const bf16x8 b = *(const bf16x8 *)&Bs[(wn + (lane & 31)) * GT_LDS + kk];
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+        }
+        __syncthreads();
+    }
+    // result lane layout: element r of lane l is row 8(r/4) + 4(l/32) + r%4, column l%32
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int row = m0 + wm + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const int col = n0 + wn + (lane & 31);
+        if (row < M && col < N) {
+            const size_t o = (size_t)row * ldc + col;
+            float v = acc[r];
+            if (accumulate) v += C[o];
+            if (bias) v += bias[col];
+            if (relu) v = fmaxf(v, 0.0f);
+            if (gate && !(gate[o] > 0.0f)) v = 0.0f;
+            C[o] = v;
         }
     }
 }
@@ -427,18 +497,39 @@ static void launch_gemm_tiles(const GemmArgs &g, int64_t tiles)
                        g.ldb, g.C, g.ldc, g.bias, g.gate, g.relu, g.accumulate);
 }
 
-// Waves over K, so that one has at most a few steps of 32 to take in turn: 16 from 1024 on, 4 from
-// 225 on. Wide tiles read A a quarter as often, but there are a quarter as many of them: they are
-// taken where that leaves two waves per SIMD (256x512x4098: 24 us narrow, 21 wide; 4098x512x256: 29
-// and 17), not below (32x256x4098: 9 us on 32 narrow tiles, 16 on 8 wide ones; 4098x256x32: 4.4 and
-// 5.5).
+// Where the lines lie (times in us, both ways measured at each):
+// - Waves over K, so that one has at most a few steps of 32 to take in turn (16 from K = 993 on, 4 from
+//   225 on), but only while the tiles leave the chip idle: at most 4 from 1024 tiles on (1024x1024x1024:
+//   29 with 16, 21 with 4, 41 with 1), one from 2048 on (4096x512x1024: 57 with 16, 41 with 4, 35 with
+//   1; 4096x2048x1024: 209, 140, 128).
+// - Wide tiles read A a quarter as often, but there are a quarter as many of them: they are taken
+//   where that leaves two waves per SIMD (256x512x4098: 24 narrow, 21 wide; 4098x512x256: 29 and 17),
+//   not below (32x256x4098: 9 on 32 narrow tiles, 16 on 8 wide ones; 4098x256x32: 4.4 and 5.5).
+// - Staged tiles where B is transposed (a lane's eight values of K are 32 bytes of a row there, and the
+//   rows are far apart) and C large enough for the longer way to them: 2048x2048x64 18 direct and 11
+//   staged, 3072x2048x1024 216 and 180, but 2048x2048x1024 145 and 170, 4096x512x256 24 and 36; and for
+//   the shortest K (3072x2048x32: 11 and 9; 3072x2048x128: 12 and 13). Also where the direct tiles'
+//   threads do not fit one dimension of a launch.
 template <bool TA, bool TB>
 static void launch_gemm(const GemmArgs &g)
 {
-    const int steps = (g.K + GT_K - 1) / GT_K, kw = steps >= 32 ? 16 : steps >= 8 ? 4 : 1;
-    const int64_t rows = (g.M + GT_ROWS - 1) / GT_ROWS;
-    const int64_t wide = rows * ((g.N + 63) / 64), narrow = rows * ((g.N + 15) / 16);
-    if (g.N >= 64 && wide * kw >= 2048) {
+    const int64_t rows = (g.M + GT_ROWS - 1) / GT_ROWS, cols = ((int64_t)g.N + 63) / 64;
+    const int64_t wide = rows * cols, narrow = rows * (((int64_t)g.N + 15) / 16);
+    const int steps = (g.K + GT_K - 1) / GT_K;
+    int kw = steps >= 32 ? 16 : steps >= 8 ? 4 : 1;
+    const bool use_wide = g.N >= 64 && wide * kw >= 2048;
+    const int64_t tiles = use_wide ? wide : narrow;
+    if (tiles >= 1024) kw = std::min(kw, 4);
+    if (tiles >= 2048) kw = 1;
+    const int64_t blocks = (rows + 3) / 4 * cols;   // of 64 x 64
+    int64_t from = INT64_MAX;   // staged from so many blocks on
+    if (TB) from = g.K <= 128 ? 512 : g.K <= 256 ? 768 : g.K <= 512 ? 1024 : 1536;
+    else if (!TA && g.K <= 64) from = g.K <= 32 ? 1024 : 1536;
+    if ((std::min(g.M, g.N) >= 64 && blocks >= from) || tiles >= (1 << 26)) {
+        hipLaunchKernelGGL((k_gemm_bf16_staged<TA, TB>), dim3((unsigned)cols, (unsigned)((rows + 3) / 4)),
+                           dim3(256), 0, g.s, g.M, g.N, g.K, g.A, g.lda, g.B, g.ldb, g.C, g.ldc,
+                           g.bias, g.gate, g.relu, g.accumulate);
+    } else if (use_wide) {
         if (kw == 16) launch_gemm_tiles<TA, TB, 4, 16>(g, wide);
         else if (kw == 4) launch_gemm_tiles<TA, TB, 4, 4>(g, wide);
         else launch_gemm_tiles<TA, TB, 4, 1>(g, wide);
