@@ -260,9 +260,21 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_staged(
     }
 }
 
-// out[j] = sum_i X[i][j] (bias gradients). A workgroup takes 64 columns, its 16 waves every 16th
-// row each, and their sums are added in wave order.
+// out[j] = sum_i X[i][j] (bias gradients), a thread per column, rows in order
+__global__ __launch_bounds__(256) void k_colsum_few(int M, int N, const float *__restrict__ X, int ldx,
+                                                    float *__restrict__ out)
+{
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= N) return;
+    float s = 0.0f;
+    for (int i = 0; i < M; ++i) s += X[(size_t)i * ldx + j];
+    out[j] = s;
+}
+
+// The same for many rows: a workgroup takes 64 columns, its 16 waves every 16th row each, and their
+// sums are added in wave order.
 #define COLSUM_WAVES 16
+#define COLSUM_ROWS 64   // fewer rows, or columns past the threads of a launch, go to k_colsum_few
 __global__ __launch_bounds__(COLSUM_WAVES * DIGS_WAVE) void k_colsum(int M, int N,
                                                                      const float *__restrict__ X,
                                                                      int ldx,
@@ -562,8 +574,14 @@ extern "C" int digs_colsum(int M, int N, const float *X, int ldx, float *out, vo
 {
     if (M < 0 || N < 0 || (N > 0 && (!X || !out || ldx < N))) return DIGS_EINVAL;
     if (N == 0) return DIGS_OK;
-    hipLaunchKernelGGL(k_colsum, dim3((N + DIGS_WAVE - 1) / DIGS_WAVE),
-                       dim3(COLSUM_WAVES * DIGS_WAVE), 0, (hipStream_t)stream, M, N, X, ldx, out);
+    // With fewer than 64 rows most of 16 waves have one or none: 16 x 2^20 takes 13 us a thread per
+    // column, 31 with 16 waves, 1 x 2^24 28 and 379; 64 x 2^18 19 and 13, 256 x 512 25 and 8.
+    if (M < COLSUM_ROWS || N >= (1 << 28))
+        hipLaunchKernelGGL(k_colsum_few, dim3((unsigned)(((int64_t)N + 255) / 256)), dim3(256), 0,
+                           (hipStream_t)stream, M, N, X, ldx, out);
+    else
+        hipLaunchKernelGGL(k_colsum, dim3((N + DIGS_WAVE - 1) / DIGS_WAVE),
+                           dim3(COLSUM_WAVES * DIGS_WAVE), 0, (hipStream_t)stream, M, N, X, ldx, out);
     return wrc(hipGetLastError());
 }
 

@@ -1,0 +1,23 @@
+"""The column sums on both sides of their dispatch: the last number of rows that a thread per column
+takes and the first that sixteen waves share, and more columns than a launch has threads for those."""
+import pytest
+import torch
+
+from paper_2506_22280_amd import _lib
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N", [(1, 257), (63, 1030), (64, 1030), (65, 63), (3, 1 << 20),
+                                 (64, (1 << 28) + 1)])
+def test_colsum_dispatch(M, N):
+    print("case: colsum M=%d N=%d" % (M, N), flush=True)
+    # whole numbers: every order of the sums is exact
+    if M * N < 1 << 28:
+        X = torch.randint(-8, 9, (M, N), device="cuda").float()
+        ref = X.sum(0)
+    else:
+        X = (torch.arange(N, device="cuda") % 7).float().expand(M, N).contiguous()
+        ref = X[0] * M
+    out = _lib.colsum(X, torch.full((N,), 7.0, device="cuda"))
+    assert torch.equal(out, ref)
