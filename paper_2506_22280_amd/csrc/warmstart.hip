@@ -271,10 +271,9 @@ __global__ __launch_bounds__(256) void k_colsum_few(int M, int N, const float *_
     out[j] = s;
 }
 
-// The same for many rows: a workgroup takes 64 columns, its 16 waves every 16th row each, and their
-// sums are added in wave order.
+// The same with the rows split: a workgroup takes 64 columns, its 16 waves every 16th row each, and
+// their sums are added in wave order.
 #define COLSUM_WAVES 16
-#define COLSUM_ROWS 64   // fewer rows, or columns past the threads of a launch, go to k_colsum_few
 __global__ __launch_bounds__(COLSUM_WAVES * DIGS_WAVE) void k_colsum(int M, int N,
                                                                      const float *__restrict__ X,
                                                                      int ldx,
@@ -574,9 +573,11 @@ extern "C" int digs_colsum(int M, int N, const float *X, int ldx, float *out, vo
 {
     if (M < 0 || N < 0 || (N > 0 && (!X || !out || ldx < N))) return DIGS_EINVAL;
     if (N == 0) return DIGS_OK;
-    // With fewer than 64 rows most of 16 waves have one or none: 16 x 2^20 takes 13 us a thread per
-    // column, 31 with 16 waves, 1 x 2^24 28 and 379; 64 x 2^18 19 and 13, 256 x 512 25 and 8.
-    if (M < COLSUM_ROWS || N >= (1 << 28))
+    // Few rows over many columns leave most of the 16 waves with one row or none, and the launch of
+    // the waves is what takes the time: 16 x 2^20 13 us a thread per column, 31 split, 1 x 2^24 28 and
+    // 379, 32 x 2^18 8 and 11; but 64 x 2^18 19 and 13, 32 x 2^16 8.5 and 7.6, 256 x 512 25 and 8. (A
+    // launch has fewer than 2^32 threads.)
+    if ((M < 64 && N > (1 << 16)) || N >= (1 << 28))
         hipLaunchKernelGGL(k_colsum_few, dim3((unsigned)(((int64_t)N + 255) / 256)), dim3(256), 0,
                            (hipStream_t)stream, M, N, X, ldx, out);
     else

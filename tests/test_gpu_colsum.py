@@ -1,5 +1,6 @@
-"""The column sums on both sides of their dispatch: the last number of rows that a thread per column
-takes and the first that sixteen waves share, and more columns than a launch has threads for those."""
+"""The column sums on both sides of their dispatch: the last numbers of rows and columns that a
+thread per column takes and the first that sixteen waves share, and more columns than a launch has
+threads for those."""
 import pytest
 import torch
 
@@ -8,7 +9,8 @@ from paper_2506_22280_amd import _lib
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,N", [(1, 257), (63, 1030), (64, 1030), (65, 63), (3, 1 << 20),
+@pytest.mark.parametrize("M,N", [(1, 257), (63, 1 << 16), (64, (1 << 16) + 1), (65, 63),
+                                 (1, (1 << 16) + 1), (63, 1 << 18),
                                  (64, (1 << 28) + 1)])
 def test_colsum_dispatch(M, N):
     print("case: colsum M=%d N=%d" % (M, N), flush=True)
