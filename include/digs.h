@@ -338,7 +338,7 @@ int digs_phi_grid(const digs_grid *grid, const float *coef, int n, const float *
  *   J^T res, res.res with J_r = (I_r - I_0)/h_r, res = I_0 - P. Fixed-order sums.
  * digs_lm_normal_eq_ws: the same on more of the chip, with the sums of slices of each view in ws
  *   (4-byte aligned, digs_lm_workspace_size bytes; 0 for small views: ws may be null). The order of
- *   the sums is fixed by npix.
+ *   the sums is fixed by R and npix.
  * digs_gemm_bf16: C[M][N] = A . B with A [M][K] (lda; transA: stored [K][M]) and B [K][N] (ldb;
  *   transB: stored [N][K]), FP32 in memory, BF16 operands on MFMA (v_mfma_f32_16x16x32_bf16), FP32
  *   accumulate; then, in order, + C if accumulate, + bias[N] if bias, max(., 0) if relu, 0 where

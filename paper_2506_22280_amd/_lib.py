@@ -657,15 +657,21 @@ def lm_normal_eq(imgs, meas, h, R: int, stream=None):
     """[T][R(R+1)/2 + R + 1] normal-equation terms from imgs [T][R+1][npix], meas [T][npix]."""
     T = meas.shape[0]
     npix = meas[0].numel() if T else 0
-    lib, n = load(), T * (R * (R + 1) // 2 + R + 1)
+    terms = R * (R + 1) // 2 + R + 1
+    lib = load()
+    if npix * (R + 2) <= 73728:   # (no workspace for views of this size)
+        out = torch.empty((T, terms), device=meas.device)
+        _check("digs_lm_normal_eq", lib.digs_lm_normal_eq(T, R, npix, _ptr(imgs), _ptr(meas), _ptr(h),
+                                                          _ptr(out), _stream(stream)))
+        return out
     # the workspace follows the result in one allocation: it lives as long as the result does
     # and, like it, belongs to whatever stream the caller runs this on
     ws_bytes = lib.digs_lm_workspace_size(T, R, npix)
-    buf = torch.empty(n + ws_bytes // 4, device=meas.device)
-    out = buf[:n].view(T, n // T if T else R * (R + 1) // 2 + R + 1)
+    buf = torch.empty(T * terms + ws_bytes // 4, device=meas.device)
+    out = buf[:T * terms].view(T, terms)
     _check("digs_lm_normal_eq", lib.digs_lm_normal_eq_ws(
-        T, R, npix, _ptr(imgs), _ptr(meas), _ptr(h), _ptr(out), buf.data_ptr() + 4 * n, ws_bytes,
-        _stream(stream)))
+        T, R, npix, _ptr(imgs), _ptr(meas), _ptr(h), _ptr(out), buf.data_ptr() + 4 * T * terms,
+        ws_bytes, _stream(stream)))
     return out
 
 

@@ -475,12 +475,13 @@ __global__ __launch_bounds__(256) void k_lm_normal_eq(int npix, int per, int nsl
 __global__ __launch_bounds__(256) void k_lm_sum(int64_t m, int nsl, const float *__restrict__ part,
                                                 float *__restrict__ out)
 {
-    const int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / DIGS_WAVE;
-    if (i >= m) return;
-    float s = 0.0f;
-    for (int k = lane_id(); k < nsl; k += DIGS_WAVE) s += part[i * nsl + k];
-    s = lm_wave_sum(s);
-    if (lane_id() == 0) out[i] = s;
+    for (int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / DIGS_WAVE; i < m;
+         i += (int64_t)gridDim.x * 4) {
+        float s = 0.0f;
+        for (int k = lane_id(); k < nsl; k += DIGS_WAVE) s += part[i * nsl + k];
+        s = lm_wave_sum(s);
+        if (lane_id() == 0) out[i] = s;
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -634,16 +635,22 @@ extern "C" int digs_standardize(int M, int N, float *X, int ldx, const float *me
     return wrc(hipGetLastError());
 }
 
-static int64_t lm_slices(int T, int npix)
+// Slices per view (a function of R and npix alone, but for results past 2^31 slices). Views of up to
+// 73728 pixels in their R + 2 images go whole: the second launch and the workspace cost more there than
+// the slices save (one view, R = 1, 16384 pixels: 4.0 us whole, 6.8 in slices, 32768 5.7 and 6.9, 65536
+// 9.0 and 6.7; R = 4, 8192 pixels 6.7 and 7.6, 16384 8.8 and 7.6).
+#define LM_WHOLE 73728
+
+static int64_t lm_slices(int T, int R, int npix)
 {
     const int64_t s = ((int64_t)npix + LM_SLICE - 1) / LM_SLICE;
-    return s <= 1 || s * T > INT32_MAX ? 1 : s;
+    return (int64_t)npix * (R + 2) <= LM_WHOLE || s * T > INT32_MAX ? 1 : s;
 }
 
 static int launch_lm(int T, int R, int npix, const float *imgs, const float *meas, const float *h,
                      float *out, float *part, hipStream_t s)
 {
-    const int nsl = part ? (int)lm_slices(T, npix) : 1, per = nsl > 1 ? LM_SLICE : npix;
+    const int nsl = part ? (int)lm_slices(T, R, npix) : 1, per = nsl > 1 ? LM_SLICE : npix;
     float *dst = nsl > 1 ? part : out;
     switch (R) {
 #define LM_CASE(r)                                                                               \
@@ -656,8 +663,8 @@ static int launch_lm(int T, int R, int npix, const float *imgs, const float *mea
     }
     if (nsl > 1) {
         const int64_t m = (int64_t)T * (R * (R + 1) / 2 + R + 1);
-        hipLaunchKernelGGL(k_lm_sum, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, m, nsl, part,
-                           out);
+        hipLaunchKernelGGL(k_lm_sum, dim3((unsigned)std::min<int64_t>((m + 3) / 4, 1 << 20)),
+                           dim3(256), 0, s, m, nsl, part, out);
     }
     return wrc(hipGetLastError());
 }
@@ -674,7 +681,7 @@ extern "C" int digs_lm_normal_eq(int T, int R, int npix, const float *imgs, cons
 extern "C" size_t digs_lm_workspace_size(int T, int R, int npix)
 {
     if (T <= 0 || R < 1 || R > DIGS_MAX_RANK || npix < 0) return 0;
-    const int64_t nsl = lm_slices(T, npix);
+    const int64_t nsl = lm_slices(T, R, npix);
     return nsl > 1 ? (size_t)T * (R * (R + 1) / 2 + R + 1) * (size_t)nsl * sizeof(float) : 0;
 }
 
