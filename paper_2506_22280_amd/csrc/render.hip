@@ -2164,8 +2164,9 @@ __device__ __forceinline__ float quad_lane(float v, int l)
                                    : __builtin_amdgcn_mov_dpp(x, 0xff, 0xf, 0xf, true));
 }
 
-// added to the cell's x index in the sources of dL/dcoef of a Gaussian with a non-finite P or Q
-#define CG_BAD (1 << 20)
+// added to the cell's x index (below 2^26) in the sources of dL/dcoef of a Gaussian with a non-finite P
+// or Q
+#define CG_BAD (1 << 28)
 
 // Four lanes per Gaussian: lane `part` adds a quarter of the chunks' fields and of V^T P, takes the
 // stencil's z index part in the second-derivative term (partial sums added in a fixed order) and
