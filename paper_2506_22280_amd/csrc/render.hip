@@ -2493,7 +2493,8 @@ __global__ __launch_bounds__(WAVES *DIGS_WAVE) void k_coef_grad(
     __shared__ __attribute__((aligned(16))) float tab[WAVES][DIGS_WAVE][CG_TAB];
     static_assert(NT * 4 <= CG_TAB, "the waves' sums take the tables' place");
     const int nbx = (g.nx + 3) >> 2, nby = (g.ny + 3) >> 2, plane = nbx * nby;
-    const int xcd = blockIdx.x & 7, b = blockIdx.x >> 3;
+    const uint32_t block = blockIdx.y * gridDim.x + blockIdx.x;
+    const int xcd = block & 7, b = block >> 3;
     const int k = (b / plane) * 8 + xcd;
     if (k >= g.nz) return;
     const int i0 = (b % plane) % nbx * 4, j0 = (b % plane) / nbx * 4;
@@ -3062,7 +3063,10 @@ static hipError_t backward_dispatch(const RenderArgs &a, float *g_mu, float *g_s
     {
         ProfScope ps(PS_COEF_GRAD, s);
         const int plane = ((a.grid.nx + 3) / 4) * ((a.grid.ny + 3) / 4);
-        const dim3 blocks((a.grid.nz + 7) / 8 * 8 * plane);
+        // (in two dimensions: one has fewer than 2^32 threads; what is past the last returns at once)
+        const uint32_t nblocks = (uint32_t)(a.grid.nz + 7) / 8 * 8 * (uint32_t)plane;
+        const uint32_t nx = std::min<uint32_t>(nblocks, 1u << 21);
+        const dim3 blocks(nx, (nblocks + nx - 1) / nx);
         // Waves per block: 16 where there are fewer than a thousand blocks, so that the fullest is
         // done sooner (20k Gaussians, 16^3 points, 256 blocks: 46 us with 8, 40 with 16), else 8, so
         // that a CU holds several blocks at different stages. Two column tiles leave registers for

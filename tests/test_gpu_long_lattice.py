@@ -43,3 +43,11 @@ def test_cells_past_2_to_the_19(R):
     print("case: 600000 control points along x, rank %d" % R, flush=True)
     nx = 600000
     _check((nx, 1, 1), (32.0 - nx, 0.0, 0.0), R, 0, nx - 64, 60)
+
+
+@pytest.mark.parametrize("dims,axis", [((1, 1, (1 << 23) + 72), 2), ((4100, 4100, 1), 1)])
+def test_blocks_past_2_to_the_32_threads(dims, axis):
+    print("case: lattice of %d x %d x %d control points" % dims, flush=True)
+    origin = [0.0, 0.0, 0.0]
+    origin[axis] = -32.0
+    _check(dims, origin, 2, axis, 4, 60)
