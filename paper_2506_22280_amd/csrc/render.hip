@@ -762,30 +762,29 @@ __device__ __forceinline__ void splat_fwd_lanes(const float4 r0, const float4 r1
 {
     const float sg = sign_of(r2.y);
     const float wu = (ent & 1u) ? sg : 0.0f, wl = (ent & 2u) ? sg : 0.0f;
-    const float la = live ? r2.z : -INFINITY;   // (log2 0: adds zero)
     const float cx = bx + 3.5f;
     const float cy = (NROWS == 8 ? by : by + ((ent & 1u) ? 0.0f : 4.0f)) + 0.5f * (float)(NROWS - 1);
-            BlockPoly b;
-            block_poly(r0, r1, r2, cx, cy, __ballot(mark_fold(r1)) != 0ull, b);
-            b.c[0] += la;
-            const float c40 = b.c[pidx(4, 0)];
+    BlockPoly b;
+    block_poly(r0, r1, r2, cx, cy, __ballot(mark_fold(r1)) != 0ull, live, b);
+    b.c[0] += r2.z;
+    const float c40 = b.c[pidx(4, 0)];
 #pragma unroll
-            for (int rp = 0; rp < NROWS / 2; ++rp) {
-                float k[2][4];
-                poly_rows(b.c, (float)rp + 0.5f, k);
+    for (int rp = 0; rp < NROWS / 2; ++rp) {
+        float k[2][4];
+        poly_rows(b.c, (float)rp + 0.5f, k);
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int r = h == 0 ? NROWS / 2 + rp : NROWS / 2 - 1 - rp;
+        for (int h = 0; h < 2; ++h) {
+            const int r = h == 0 ? NROWS / 2 + rp : NROWS / 2 - 1 - rp;
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        float xp, xm;
-                        poly_cols(k[h], c40, (float)c + 0.5f, xp, xm);
-                        add_pixel<NROWS>(acc, r, 4 + c, __builtin_amdgcn_exp2f(xp), wu, wl);
-                        add_pixel<NROWS>(acc, r, 3 - c, __builtin_amdgcn_exp2f(xm), wu, wl);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);   // (a row at a time: registers)
-                }
+            for (int c = 0; c < 4; ++c) {
+                float xp, xm;
+                poly_cols(k[h], c40, (float)c + 0.5f, xp, xm);
+                add_pixel<NROWS>(acc, r, 4 + c, __builtin_amdgcn_exp2f(xp), wu, wl);
+                add_pixel<NROWS>(acc, r, 3 - c, __builtin_amdgcn_exp2f(xm), wu, wl);
             }
+            __builtin_amdgcn_sched_barrier(0);   // (a row at a time: registers)
+        }
+    }
 }
 
 // Evaluates cnt queued Gaussians from position head of the queue q (mask: its size less one for a
@@ -1073,12 +1072,6 @@ __device__ __forceinline__ float splat_fwd_block(const float4 *__restrict__ rt,
                     if (dir) q2[n2 + lane_rank(dm)] = ent;
                     n2 += __popcll(dm);
                     wave_sync_lds();
-                    // (their lanes idle with an empty record: their own series need not be
-                    // finite, and would reach every pixel of the block)
-                    if (mark_direct(r0)) {
-                        r0 = r1 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                        r2 = idle_rec2();
-                    }
                     if (n2 >= DIGS_WAVE) {
                         splat_fwd_cols(rt, q2, 0, n2, ~0, lane, fx, fy, accc);
                         n2 = 0;
@@ -1432,7 +1425,7 @@ __device__ __forceinline__ void splat_bwd_poly(const float4 r0, const float4 r1,
 {
 #pragma clang fp contract(off)
     BlockPoly b;
-    block_poly(r0, r1, r2, cx, cy, __ballot(mark_fold(r1)) != 0ull, b);
+    block_poly(r0, r1, r2, cx, cy, __ballot(mark_fold(r1)) != 0ull, true, b);
     float M[15];
 #pragma unroll
     for (int k = 0; k < 15; ++k) M[k] = 0.0f;

@@ -82,9 +82,10 @@ __device__ __forceinline__ bool mark_fold(const float4 r1) { return signbit(r1.w
 __device__ __forceinline__ bool mark_direct(const float4 r0) { return !signbit(r0.z); }
 
 // The series of one record about the block centre (cx, cy) in pixel-index coordinates; fold
-// (uniform over the wave): with the degree-5 terms.
+// (uniform over the wave): with the degree-5 terms. Not live: the series of log2 0, minus infinity
+// everywhere, whatever the record's own would be (a record marked direct need not have a finite one).
 __device__ __forceinline__ void block_poly(const float4 r0, const float4 r1, const float4 r2,
-                                           float cx, float cy, bool fold, BlockPoly &b)
+                                           float cx, float cy, bool fold, bool live, BlockPoly &b)
 {
     const float Huu = -fabsf(r0.z), Huv = r0.w, Hvv = r1.x, gu = r1.y, gv = r1.z, Guu = fabsf(r1.w);
     const float Guv = r2.x, Gvv = fabsf(r2.y);
@@ -96,7 +97,7 @@ __device__ __forceinline__ void block_poly(const float4 r0, const float4 r1, con
     const float tq = fmaf(Guv, dv, fmaf(Guu, du, gu)), nq = fmaf(Gvv, dv, gv);
     const float q00 = fmaf(dv, nq, fmaf(du, tq, 1.0f)), q10 = fmaf(Guu, du, tq);
     const float q01 = fmaf(Guv, du, fmaf(Gvv, dv, nq));
-    const float rs = __builtin_amdgcn_rsqf(q00), iq = rs * rs;
+    const float rs = live ? __builtin_amdgcn_rsqf(q00) : 0.0f, iq = rs * rs;
     b.iq = iq;
     b.lrs = __builtin_amdgcn_logf(rs);
     const float p10 = q10 * iq, p01 = q01 * iq, p20 = Guu * iq, p11 = Guv * iq, p02 = Gvv * iq;
