@@ -96,11 +96,13 @@ __global__ __launch_bounds__(KW == 16 ? 1024 : 256) void k_gemm_bf16(
     __shared__ __attribute__((aligned(16))) float red[KW == 1 ? 1 : KW * GT_ROWS * COLS];
     const int wave = threadIdx.x / DIGS_WAVE, lane = lane_id();
     const int ntn = (N + COLS - 1) / COLS, ntm = (M + GT_ROWS - 1) / GT_ROWS;
-    const int64_t tile = (int64_t)blockIdx.x * NT + (KW == 1 ? wave : 0);
-    const bool have = tile < (int64_t)ntn * ntm;   // (false only with KW == 1)
+    // (launch_gemm: fewer than 2^26 tiles)
+    const uint32_t tile = blockIdx.x * NT + (KW == 1 ? wave : 0);
+    const bool have = tile < (uint32_t)ntn * (uint32_t)ntm;   // (false only with KW == 1)
     const bool down = N > M && (M >= 1024 || N >= 65536);
-    const int m0 = have ? (int)(down ? tile % ntm : tile / ntn) * GT_ROWS : 0;
-    const int n0 = have ? (int)(down ? tile / ntm : tile % ntn) * COLS : 0;
+    const uint32_t line = have ? tile / (uint32_t)(down ? ntm : ntn) : 0u;
+    const uint32_t step = have ? tile - line * (uint32_t)(down ? ntm : ntn) : 0u;
+    const int m0 = (int)(down ? step : line) * GT_ROWS, n0 = (int)(down ? line : step) * COLS;
     const int kw = KW == 1 ? 0 : wave, kl = 8 * (lane >> 4);
     const float *pa[1], *pb[TN];
     const int row = min(m0 + (lane & 15), M - 1);
