@@ -34,7 +34,8 @@ sys.path.insert(0, ROOT)
 METRIC = "fwd+bwd projections/s @200k Gaussians 512×384 det; % HBM roofline; speedup vs plain"
 
 # Algorithmic FP32 work per (Gaussian, pixel) pair inside a cut-off footprint, in the splats'
-# forward-difference formulation (FMA = 2 FLOP, add/mul = 1, rsqrt/exp2 = 1), and the VALU issue
+# forward-difference formulation, which stays the measure of the work although the block polynomial
+# of the exact model needs less (FMA = 2 FLOP, add/mul = 1, rsqrt/exp2 = 1), and the VALU issue
 # slots it needs: forward 4 adds (q, dq, E, dE), r^2, x = E r^2 + log2 amp (FMA), the sum (FMA),
 # rsqrt and exp2 (7 VALU ops, 2 transcendentals); backward the same evaluation (r^2, x, g r 2^x:
 # 3 muls; a = . r^2, a x: 2 muls) plus its moment sums (3 adds and 4 FMAs per pixel: 17 VALU ops,
@@ -61,9 +62,9 @@ ALGO_BYTES_PER_STEP = ALGO_BYTES_PER_PROJ * 64   # 129.7 MB per 64-view fwd+bwd 
 # bench (FETCH_SIZE, then WRITE_SIZE, mean KiB per dispatch, scaled by what the same counters read
 # for a 512 MiB device copy: x2.0 and x1.0; profiles/batched_200k_hbm_counters.md), taken on the
 # library sources whose digest is given; reported only while their code (comments aside) is unchanged
-TRAFFIC = {"kernel": "k_splat_bwd", "read_bytes": 2219897.6 * (524288.0 / 262166.5625) * 1024,
-           "write_bytes": 6624472.5 * 1.000 * 1024,
-           "sources_sha256": "cae9094998698b08728fd85aeb2bfaded4df50dc64d9a9cf70e53e5c95fb4d58"}
+TRAFFIC = {"kernel": "k_splat_bwd", "read_bytes": 2004043.584375 * (524288.0 / 262157.5) * 1024,
+           "write_bytes": 6738636.3875 * 1.000 * 1024,
+           "sources_sha256": "7b8ea8b273b3325e3672c06ad13e0e6380240b4ac101a7d9a726413273ba318b"}
 
 
 def sources_digest() -> str:
@@ -609,7 +610,7 @@ def main():
                            "pairs_per_launch": int(per_launch_pairs),
                            "flop_per_pair": flop,
                            "op_mix": {"peak": round(mix, 2), "frac": round(achieved / mix, 4),
-                                      "meaning": "unpacked VALU issue rate for this kernel's "
+                                      "meaning": "unpacked VALU issue rate for direct evaluation's "
                                                  "per-pair mix (transcendentals two slots)"},
                            "algorithmic_bytes_per_step": int(ALGO_BYTES_PER_STEP),
                            "traffic_over_algorithmic": (round(traffic / ALGO_BYTES_PER_STEP, 2)

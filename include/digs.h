@@ -91,9 +91,10 @@ typedef struct digs_tuning {
     int splat_waves;         /* forward splat: waves per tile, 4 (one per 8x8 block, at most as
                                 many as the tile has blocks) or 1 (default 4)                  */
     int slices;              /* workgroups per tile list in the splats, 1..DIGS_MAX_SLICES; 0: by
-                                shape (1 when the call has >= 2048 (view, tile) items, else
-                                enough for about 2048 workgroups, at most 8, or more if the lists
-                                are expected to be long). Another value adds
+                                shape ((view, tile) items of the call: from 2048 on 1; from 1024
+                                one for every 700 list entries expected, at least 1; below 1024
+                                enough for about 2048 workgroups, at most 8, or one for every 600
+                                entries expected if that is more). Another value adds
                                 the same terms in another order (results bitwise reproducible
                                 for one value). With slices > 1 the splats are not persistent. */
     int persistent;          /* 1: splats run as persistent kernels over per-XCD work queues of

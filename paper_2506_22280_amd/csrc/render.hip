@@ -716,9 +716,9 @@ __device__ __forceinline__ void slice_range(uint32_t &begin, uint32_t &end, int 
 // one and each pixel 2.5 multiply-adds, an exp2 and one more multiply-add: 430 instructions for 64
 // Gaussians' blocks, against 8 x 84 by columns (a reciprocal square root, an exp2 and seven others
 // per pixel). By the same count a remainder of up to FWD_COLS Gaussians is cheaper by columns.
-// Measured against columns for all of them: 4.72 -> 3.70 ms (200k Gaussians, 64 views of 512x384),
-// 5.75 -> 4.33 (500k, 16 views of 1024x768), 127 -> 83 us (80k, 512x512). Without the queue of
-// halves the first takes 3.80 ms. A block many of whose Gaussians are direct stays with the columns
+// Measured against columns for all of them, in turn: 4.72 -> 3.72 ms (200k Gaussians, 64 views of
+// 512x384), 5.77 -> 4.30 (500k, 16 views of 1024x768), 127 -> 94 us (80k, 512x512). Without the queue
+// of halves the first takes 0.1 ms more. A block many of whose Gaussians are direct stays with the columns
 // (splat_fwd_tile).
 //
 // The EWA model goes by columns throughout: a pixel there is an exp2 and three others already, and
@@ -1186,11 +1186,14 @@ __device__ __forceinline__ void splat_fwd_tile(const DevGeom &G, int n, int t, i
             // A block of whose first 64 entries more than 8 are marked direct goes by columns
             // throughout: setting them aside costs more than the lanes gain (58k Gaussians, 20
             // views of 86x55 pixels of 4.5 mm, nearly all direct: 144 us by this rule, 185 without
-            // it; 200k on 1 mm pixels, nearly none: 4.72 ms by columns, 3.70 by this rule). So does
+            // it; 200k on 1 mm pixels, nearly none: 4.72 ms by columns, 3.72 by this rule). So does
             // a list of fewer than FWD_SHORT entries, about two groups of 64 a block, without a look
-            // at its records: there the lanes' sums and remainder cost what they gain (one 256x256
-            // view of 50k Gaussians, about 290 entries: 48 us by lanes, 45 by columns; 375 entries,
-            // 16 views of 64x64: 35.0 and 34.5; 940, 512x512: 83 by lanes, 96 by columns in quarters)
+            // at its records: there the lanes' sums and remainder cost about what they gain. Forward
+            // calls by this rule / by lanes for every list: batches of 3k Gaussians 675 / 657 us, 12k
+            // 866 / 886, 25k 1054 / 1078, 50k on 16 views of 256x192 434-451 / 453; lists of four views of
+            // 512x384 cut to that length, 200k Gaussians: 492 entries 846 / 697 (by columns / by
+            // lanes), 246 874 / 755, 123 933 / 868, and of 50k, 59 entries, 557 / 564 (by
+            // default such calls do not cut their lists).
             uint32_t first = LIST_INDEX_MASK;
             bool cols = end - begin < FWD_SHORT;
             if (!cols) {
@@ -1416,8 +1419,8 @@ struct BwdShared {
 // columns in pairs at +-s, so that the even and odd parts of the exponent and of the moments are
 // each computed once for two pixels. VALU-bound: an 8-row pair takes 14 instructions per pixel
 // (one transcendental) against 20 (two) by forward differences, which stay for groups that hold a
-// record marked direct. 200k Gaussians, 512x384, 64 views: 8.53 -> 6.64 ms; 500k, 1024x768, 16
-// views: 10.4 -> 7.84 ms. 78 VGPRs; the 40 KB of LDS hold it to four waves per SIMD.
+// record marked direct. 200k Gaussians, 512x384, 64 views, in turn: 8.4-8.6 -> 6.8-7.1 ms; 500k, 1024x768,
+// 16 views: 10.3 -> 8.1 ms. 78 VGPRs; the 40 KB of LDS hold it to four waves per SIMD.
 template <int NROWS, int GS>
 __device__ __forceinline__ void splat_bwd_poly(const float4 r0, const float4 r1, const float4 r2,
                                                const float *__restrict__ gp, float cx, float cy,
@@ -2433,7 +2436,9 @@ __global__ void k_cell_start(int n, int ncells, const uint32_t *__restrict__ key
 //
 // A wave per control point read every Gaussian 64 times, a lane each (168 bytes at R = 3, one cache
 // line per lane and load); a block reads it 12 times, coalesced. Blocks of a lattice plane go to one
-// XCD: neighbours in the plane share most of their Gaussians in its L2.
+// XCD: neighbours in the plane share most of their Gaussians in its L2. At rank 2, six of 16 columns,
+// phantoms take 0.94 to 1.6 times less than with a wave per point; Gaussians spread evenly, 50 to 1000
+// a block, up to 18% more (15k, 29^3 points: 22 -> 27 us).
 // Measured against a wave per control point: 398 -> 171 us (200k Gaussians, 29^3 points, R = 3), 972
 // -> 287 (500k, 35^3, R = 4), 62 -> 40 (20k, 16^3), 72 -> 61 (80k, 29^3, R = 2). The products are a
 // third of the time, the pieces and the addresses most of the rest; the fullest block holds seven
@@ -3061,9 +3066,11 @@ static hipError_t backward_dispatch(const RenderArgs &a, float *g_mu, float *g_s
         const uint32_t nx = std::min<uint32_t>(nblocks, 1u << 21);
         const dim3 blocks(nx, (nblocks + nx - 1) / nx);
         // Waves per block: 16 where there are fewer than a thousand blocks, so that the fullest is
-        // done sooner (20k Gaussians, 16^3 points, 256 blocks: 46 us with 8, 40 with 16), else 8, so
-        // that a CU holds several blocks at different stages. Two column tiles leave registers for
-        // 8 only.
+        // done sooner, else 8, so that a CU holds several blocks at different stages. The backward
+        // call at rank 3, 8 / 16 waves: 256 blocks, 20k Gaussians 124 / 118 us, 80k 301 / 272; 828
+        // blocks, 8k 81 / 84, 20k 105 / 103, 80k 207 / 185; 1323 blocks, 8k 84 / 95, 20k 98 / 104, 80k
+        // 190 / 182; 1856 blocks, 8k 90 / 102, 80k level; 2835 blocks, 80k 171 / 188.
+        // Two column tiles leave registers for 8 only.
         const float *gq = WS(a, gq, const float *);
         const uint32_t *cells = WS(a, cell_start, const uint32_t *);
         if constexpr (NR == 1)
