@@ -715,11 +715,13 @@ __device__ __forceinline__ void slice_range(uint32_t &begin, uint32_t &end, int 
 // VALU-bound. A lane per Gaussian makes the set-up of its polynomial (80 instructions) a 64-pixel
 // one and each pixel 2.5 multiply-adds, an exp2 and one more multiply-add: 430 instructions for 64
 // Gaussians' blocks, against 8 x 84 by columns (a reciprocal square root, an exp2 and seven others
-// per pixel). By the same count a remainder of up to FWD_COLS Gaussians is cheaper by columns.
+// per pixel). By the same count a remainder of up to FWD_COLS Gaussians is cheaper by columns. By
+// hardware counters at 200k Gaussians, with the lists' walk and all: 8.9 per evaluated pixel (by
+// columns 11.8), the issue slots full, 14.3 wavefronts per CU of the 16 that 127 VGPRs allow.
 // Measured against columns for all of them, in turn: 4.72 -> 3.72 ms (200k Gaussians, 64 views of
-// 512x384), 5.77 -> 4.30 (500k, 16 views of 1024x768), 127 -> 94 us (80k, 512x512). Without the queue
-// of halves the first takes 0.1 ms more. A block many of whose Gaussians are direct stays with the columns
-// (splat_fwd_tile).
+// 512x384), 5.77 -> 4.30 (500k, 16 views of 1024x768), 127 -> 94 us (80k, 512x512). Without the
+// queue of halves the first takes 0.1 ms more. A block many of whose Gaussians are direct stays with
+// the columns (splat_fwd_tile).
 //
 // The EWA model goes by columns throughout: a pixel there is an exp2 and three others already, and
 // the lanes' sums of a block cost more than they gain where lists are short (200k Gaussians, 16
@@ -1190,10 +1192,10 @@ __device__ __forceinline__ void splat_fwd_tile(const DevGeom &G, int n, int t, i
             // a list of fewer than FWD_SHORT entries, about two groups of 64 a block, without a look
             // at its records: there the lanes' sums and remainder cost about what they gain. Forward
             // calls by this rule / by lanes for every list: batches of 3k Gaussians 675 / 657 us, 12k
-            // 866 / 886, 25k 1054 / 1078, 50k on 16 views of 256x192 434-451 / 453; lists of four views of
-            // 512x384 cut to that length, 200k Gaussians: 492 entries 846 / 697 (by columns / by
-            // lanes), 246 874 / 755, 123 933 / 868, and of 50k, 59 entries, 557 / 564 (by
-            // default such calls do not cut their lists).
+            // 866 / 886, 25k 1054 / 1078, 50k on 16 views of 256x192 434-451 / 453; by columns / by
+            // lanes, lists of four views of 512x384 cut to that length (the default does not): 200k
+            // Gaussians, 492 entries 846 / 697, 246 874 / 755, 123 933 / 868; 50k, 59 entries 557 /
+            // 564.
             uint32_t first = LIST_INDEX_MASK;
             bool cols = end - begin < FWD_SHORT;
             if (!cols) {
@@ -1419,8 +1421,9 @@ struct BwdShared {
 // columns in pairs at +-s, so that the even and odd parts of the exponent and of the moments are
 // each computed once for two pixels. VALU-bound: an 8-row pair takes 14 instructions per pixel
 // (one transcendental) against 20 (two) by forward differences, which stay for groups that hold a
-// record marked direct. 200k Gaussians, 512x384, 64 views, in turn: 8.4-8.6 -> 6.8-7.1 ms; 500k, 1024x768,
-// 16 views: 10.3 -> 8.1 ms. 78 VGPRs; the 40 KB of LDS hold it to four waves per SIMD.
+// record marked direct; with set-up, slot sums and partials 17.5 against 22.3 by hardware counters.
+// 200k Gaussians, 512x384, 64 views, in turn: 8.4-8.6 -> 6.8-7.1 ms; 500k, 1024x768, 16 views: 10.3 ->
+// 8.1 ms. 78 VGPRs; the 40 KB of LDS hold it to four waves per SIMD.
 template <int NROWS, int GS>
 __device__ __forceinline__ void splat_bwd_poly(const float4 r0, const float4 r1, const float4 r2,
                                                const float *__restrict__ gp, float cx, float cy,
