@@ -1190,12 +1190,14 @@ __device__ __forceinline__ void splat_fwd_tile(const DevGeom &G, int n, int t, i
             // views of 86x55 pixels of 4.5 mm, nearly all direct: 144 us by this rule, 185 without
             // it; 200k on 1 mm pixels, nearly none: 4.72 ms by columns, 3.72 by this rule). So does
             // a list of fewer than FWD_SHORT entries, about two groups of 64 a block, without a look
-            // at its records: there the lanes' sums and remainder cost about what they gain. Forward
-            // calls by this rule / by lanes for every list: batches of 3k Gaussians 675 / 657 us, 12k
-            // 866 / 886, 25k 1054 / 1078, 50k on 16 views of 256x192 434-451 / 453; by columns / by
-            // lanes, lists of four views of 512x384 cut to that length (the default does not): 200k
-            // Gaussians, 492 entries 846 / 697, 246 874 / 755, 123 933 / 868; 50k, 59 entries 557 /
-            // 564.
+            // at its records: there the lanes' sums and remainder cost about what they gain. With the
+            // line at 400 / 200, one 256x256 view in 8 slices, the scan's 50k at 1.6 mm (about 150
+            // entries each, 290 in the middle) 84.6 / 86.8 us, but 50k at 0.8 mm (231) 160 / 151, 20k
+            // on 190x141x5 166 / 155. By this rule / by lanes for every list: batches of 3k Gaussians
+            // 675 / 657, 12k 866 / 886, 25k 1054 / 1078, 50k on 16 views of 256x192 434-451 / 453. By
+            // columns / by lanes, lists of four views of 512x384 cut to that length (the default does
+            // not): 200k Gaussians, 492 entries 846 / 697, 246 874 / 755, 123 933 / 868; 50k, 59
+            // entries 557 / 564.
             uint32_t first = LIST_INDEX_MASK;
             bool cols = end - begin < FWD_SHORT;
             if (!cols) {
